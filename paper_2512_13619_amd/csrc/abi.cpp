@@ -416,12 +416,19 @@ hdg_status hdg_element_blocks_sys(hdg_ctx ctx, const hdg_dims* dims, const hdg_e
     if (element_sys_lds_bytes(dims, g->nqv, g->nqf) > 150 * 1024)
         return set_err(ctx, HDG_ERR_SHAPE, "hdg_element_blocks_sys: element data exceed 150 KiB of LDS");
     HDG_HIP_CHECK(ctx, hipSetDevice(ctx->device));
-    const size_t per = element_sys_ws_doubles(dims, g->nqv, g->nqf);
-    int64_t chunk = (int64_t)(((size_t)1 << 30) / (per * sizeof(double)));
-    if (chunk < 1) chunk = 1;
-    if (chunk > dims->ne) chunk = dims->ne;
-    double* ws = (double*)ws_get(ctx, WS_ELEM_SYS, sizeof(double) * per * (size_t)chunk, &st);
-    if (!ws) return st;
+    // the point workspace holds flux derivatives only: a residual needs none, and one launch
+    int64_t chunk = dims->ne;
+    double* ws = nullptr;
+    if (!residual_only) {
+        const size_t per = element_sys_ws_doubles(dims, g->nqv, g->nqf);
+        chunk = (int64_t)(((size_t)1 << 31) / (per * sizeof(double)));
+        if (chunk < 1) chunk = 1;
+        // equal chunks: a short last one would leave most of the chip idle
+        const int64_t launches = (dims->ne + chunk - 1) / chunk;
+        chunk = (dims->ne + launches - 1) / launches;
+        ws = (double*)ws_get(ctx, WS_ELEM_SYS, sizeof(double) * per * (size_t)chunk, &st);
+        if (!ws) return st;
+    }
     int* status = (int*)ws_get(ctx, WS_STATUS, 64, &st);
     if (!status) return st;
     const int big = 0x7fffffff;

@@ -12,6 +12,12 @@ __device__ __forceinline__ double dpp_mov(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// v of lane N of this lane's row of 16.
+template <int N>
+__device__ __forceinline__ double row_bcast(double v) {
+    return dpp_mov<0x150 + N>(v);    // row_newbcast:N
+}
+
 __device__ __forceinline__ double read_lane(double v, int l) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
                             __builtin_amdgcn_readlane(__double2loint(v), l));
@@ -58,6 +64,35 @@ __device__ __forceinline__ double wave_sum_all(double v) {
     v += dpp_mov<0x141>(v);   // row_half_mirror
     v += dpp_mov<0x140>(v);   // row_mirror
     return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
+}
+
+// acc += A B for one 16 x 16 tile over K terms on the FP64 matrix cores (v_mfma_f64_16x16x4f64:
+// A[i][k] in lane i+16k, B[k][j] in lane j+16k; the result's entry (i, j) in lane
+// j+16(i mod 4), register i div 4). fa(k) gives this lane's A[lane mod 16][k], fb(k) its
+// B[k][lane mod 16], with k in [0, K); terms past K are zero on both sides. U steps' loads
+// are issued together.
+typedef double d4 __attribute__((ext_vector_type(4)));
+template <int U, class FA, class FB>
+__device__ __forceinline__ void mma16(int K, const FA& fa, const FB& fb, d4& acc) {
+    const int kq = (threadIdx.x & 63) >> 4;
+    int k0 = 0;
+    for (; k0 + 4 * U <= K; k0 += 4 * U) {
+        double a[U], b[U];
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+            a[s] = fa(k0 + 4 * s + kq);
+            b[s] = fb(k0 + 4 * s + kq);
+        }
+#pragma unroll
+        for (int s = 0; s < U; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
+    }
+    for (; k0 < K; k0 += 4) {
+        const int k = k0 + kq, kc = k < K ? k : K - 1;
+        double a = fa(kc), b = fb(kc);
+        a = k < K ? a : 0.0;
+        b = k < K ? b : 0.0;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+    }
 }
 
 // res[r] = sum_{k<n} A[(i0+r)*lda + k] v[k] for r < nr (nr <= 4), v in LDS; the loads of
