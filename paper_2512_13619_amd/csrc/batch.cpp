@@ -62,9 +62,9 @@ hdg_status hdg_batch_create(hdg_ctx ctx, int32_t n_inst, const hdg_dims* dims_h,
     b->offs.assign(A_NARR, std::vector<int64_t>(n_inst + 1, 0));
     std::vector<int32_t> eid, fid, dof_inst, blk_inst, ib0(n_inst), ib1(n_inst);
     std::vector<int64_t> blk_lo, blk_hi;
+    std::vector<FaceBlk> fblk;
     int64_t e0 = 0, f0 = 0;
     size_t max_cond = 0, max_rec = 0;
-    const int64_t CH = 2048;
     for (int i = 0; i < n_inst; ++i) {
         const hdg_dims& d = dims_h[i];
         if (d.ne < 1 || d.nf < 1 || d.ncomp < 1 || d.dim < 1 || d.dim > 3 || d.npe < 1 || d.npf < 1 || d.nlfe < 2 ||
@@ -116,11 +116,13 @@ hdg_status hdg_batch_create(hdg_ctx ctx, int32_t n_inst, const hdg_dims* dims_h,
         fid.insert(fid.end(), q.nf, i);
         const int64_t n = (int64_t)q.nf * q.nb;
         dof_inst.insert(dof_inst.end(), n, i);
+        const int lteam = batch_team(q.nb, q.S);
+        for (int f = 0; f < q.nf; f += 256 >> lteam) fblk.push_back({i, f, lteam, 0});
         ib0[i] = (int32_t)blk_inst.size();
-        for (int64_t k = 0; k < n; k += CH) {
+        for (int64_t k = 0; k < n; k += SEG_CHUNK) {
             blk_inst.push_back(i);
             blk_lo.push_back(q.vec_off + k);
-            blk_hi.push_back(q.vec_off + std::min(n, k + CH));
+            blk_hi.push_back(q.vec_off + std::min<int64_t>(n, k + SEG_CHUNK));
         }
         ib1[i] = (int32_t)blk_inst.size();
         b->dev.max_nb = std::max(b->dev.max_nb, q.nb);
@@ -138,6 +140,8 @@ hdg_status hdg_batch_create(hdg_ctx ctx, int32_t n_inst, const hdg_dims* dims_h,
     if (err == hipSuccess) dv.desc = dev_upload(b, b->host, &err);
     if (err == hipSuccess) dv.eid = dev_upload(b, eid, &err);
     if (err == hipSuccess) dv.fid = dev_upload(b, fid, &err);
+    dv.nfblk = (int)fblk.size();
+    if (err == hipSuccess) dv.fblk = dev_upload(b, fblk, &err);
     if (err == hipSuccess) dv.dof_inst = dev_upload(b, dof_inst, &err);
     if (err == hipSuccess) dv.blk_inst = dev_upload(b, blk_inst, &err);
     if (err == hipSuccess) dv.blk_lo = dev_upload(b, blk_lo, &err);
@@ -431,9 +435,10 @@ hdg_status hdg_gmres_solve_batch(hdg_ctx ctx, hdg_batch b, const double* K64, co
     if (!V) return st;
     double* Z = (double*)ws_get(ctx, WS_KRYLOV_Z, sizeof(double) * ld * m, &st);
     if (!Z) return st;
-    double* part = (double*)ws_get(ctx, WS_PART, sizeof(double) * (size_t)dv.nblk * (m + 2), &st);
+    double* part = (double*)ws_get(ctx, WS_PART, sizeof(double) * (size_t)dv.nblk * (m + 1) * 2, &st);
     if (!part) return st;
-    const size_t nctl = (size_t)ni * ((size_t)ldh * m + 6 * (size_t)ldg + 2);
+    double* part2 = part + (size_t)dv.nblk * (m + 1);     // a sweep reads the partials of the one before
+    const size_t nctl = (size_t)ni * ((size_t)ldh * m + 5 * (size_t)ldg + 2);
     char* base = (char*)ws_get(ctx, WS_CTL, sizeof(BatchCtl) * ni + sizeof(double) * nctl, &st);
     if (!base) return st;
     BatchCtl* ctl = (BatchCtl*)base;
@@ -442,8 +447,7 @@ hdg_status hdg_gmres_solve_batch(hdg_ctx ctx, hdg_batch b, const double* K64, co
     double* sn = cs + (size_t)ni * ldg;
     double* g = sn + (size_t)ni * ldg;
     double* y = g + (size_t)ni * ldg;
-    double* h2 = y + (size_t)ni * ldg;
-    double* bn = h2 + (size_t)ni * ldg;       // ||b||^2 per instance
+    double* bn = y + (size_t)ni * ldg;       // ||b||^2 per instance
     double* target = bn + (size_t)ni * ldg;   // per-instance absolute target
     const void* Kop = mixed ? (const void*)K32 : (const void*)K64;
     const void* Bop = nullptr;
@@ -474,7 +478,7 @@ hdg_status hdg_gmres_solve_batch(hdg_ctx ctx, hdg_batch b, const double* K64, co
     }
     // per-instance ||b||
     if ((st = seg_sumsq(ctx, dv, rhs, part, nullptr)) != HDG_OK) return st;
-    if ((st = seg_reduce(ctx, dv, part, 1, bn, ldg, false, nullptr, 0, nullptr)) != HDG_OK) return st;
+    if ((st = seg_reduce(ctx, dv, part, bn, ldg)) != HDG_OK) return st;
     std::vector<double> bn_h((size_t)ni * ldg), tg_h((size_t)ni * ldg, 0.0);
     HDG_HIP_CHECK(ctx, hipMemcpyAsync(bn_h.data(), bn, sizeof(double) * bn_h.size(), hipMemcpyDeviceToHost,
                                       ctx->stream));
@@ -493,37 +497,45 @@ hdg_status hdg_gmres_solve_batch(hdg_ctx ctx, hdg_batch b, const double* K64, co
     const int ld_beta = (int)(sizeof(BatchCtl) / sizeof(double));
     auto enqueue_cycle = [&](int jmax) -> hdg_status {
         hdg_status s2;
-        if ((s2 = batch_launch_face(ctx, dv, K64, false, nbr, false, x, V, -1.0, rhs, 1.0, nullptr)) != HDG_OK) return s2;
+        if ((s2 = batch_launch_face(ctx, dv, K64, false, nbr, false, x, V, -1.0, rhs, 1.0, nullptr, 0, nullptr)) != HDG_OK)
+            return s2;
         if ((s2 = seg_sumsq(ctx, dv, V, part, nullptr)) != HDG_OK) return s2;
         if ((s2 = seg_cycle_init(ctx, dv, part, ctl, g, ldg, jmax, target)) != HDG_OK) return s2;
-        if ((s2 = seg_scale(ctx, dv, V, &ctl[0].beta, ld_beta, ctl)) != HDG_OK) return s2;
         for (int j = 0; j < jmax; ++j) {
             double* vj = V + (size_t)j * ld;
             double* zj = Z + (size_t)j * ld;
             double* wv = V + (size_t)(j + 1) * ld;
-            if (Bop) {
-                if ((s2 = batch_launch_face(ctx, dv, Bop, mixed, nullptr, true, vj, zj, 1.0, nullptr, 0.0, ctl)) != HDG_OK)
-                    return s2;
-            } else if ((s2 = vec_lincomb(ctx, N, zj, 1.0, vj, 0.0, nullptr, nullptr)) != HDG_OK) {
-                return s2;
-            }
-            if ((s2 = batch_launch_face(ctx, dv, Kop, mixed, nbr, false, zj, wv, 1.0, nullptr, 0.0, ctl)) != HDG_OK)
-                return s2;
             double* col = H + (size_t)j * ldh;
-            if ((s2 = seg_multidot(ctx, dv, V, ld, j + 1, wv, part, ctl)) != HDG_OK) return s2;
-            if ((s2 = seg_reduce(ctx, dv, part, j + 1, col, ldh * m, false, nullptr, 0, ctl)) != HDG_OK) return s2;
-            if ((s2 = seg_multiaxpy(ctx, dv, V, ld, j + 1, col, ldh * m, -1.0, wv, ctl, false)) != HDG_OK) return s2;
-            if (o->orth == HDG_ORTH_CGS2) {
-                if ((s2 = seg_multidot(ctx, dv, V, ld, j + 1, wv, part, ctl)) != HDG_OK) return s2;
-                if ((s2 = seg_reduce(ctx, dv, part, j + 1, col, ldh * m, true, h2, ldg, ctl)) != HDG_OK) return s2;
-                if ((s2 = seg_multiaxpy(ctx, dv, V, ld, j + 1, h2, ldg, -1.0, wv, ctl, false)) != HDG_OK) return s2;
+            // v_j arrives not yet normalised: its norm is beta or the last column's subdiagonal entry
+            const double* denom = j == 0 ? &ctl[0].beta : col - ldh + j;
+            const int ld_denom = j == 0 ? ld_beta : ldh * m;
+            if (Bop) {
+                if ((s2 = batch_launch_face(ctx, dv, Bop, mixed, nullptr, true, vj, zj, 1.0, nullptr, 0.0, denom, ld_denom,
+                                            ctl)) != HDG_OK)
+                    return s2;
+            } else {
+                if ((s2 = seg_scale(ctx, dv, vj, denom, ld_denom, ctl)) != HDG_OK) return s2;
+                if ((s2 = vec_lincomb(ctx, N, zj, 1.0, vj, 0.0, nullptr, nullptr)) != HDG_OK) return s2;
             }
-            if ((s2 = seg_sumsq(ctx, dv, wv, part, ctl)) != HDG_OK) return s2;
-            if ((s2 = seg_givens(ctx, dv, part, ctl, H, ldh, m, cs, sn, g, ldg, j, jmax, target)) != HDG_OK) return s2;
-            if ((s2 = seg_scale(ctx, dv, wv, col + j + 1, ldh * m, ctl)) != HDG_OK) return s2;
+            if ((s2 = batch_launch_face(ctx, dv, Kop, mixed, nbr, false, zj, wv, 1.0, nullptr, 0.0, nullptr, 0, ctl)) !=
+                HDG_OK)
+                return s2;
+            SegSweep sw{};
+            sw.V = V; sw.ldv = ld; sw.J = j + 1; sw.w = wv; sw.part_out = part;
+            sw.col = col; sw.ld_col = ldh * m; sw.ctl = ctl;
+            if ((s2 = seg_sweep(ctx, dv, sw, false, true)) != HDG_OK) return s2;
+            if (o->orth == HDG_ORTH_CGS2) {
+                sw.part_in = part; sw.part_out = part2;
+                if ((s2 = seg_sweep(ctx, dv, sw, true, true)) != HDG_OK) return s2;
+                sw.add = 1;
+            }
+            sw.part_in = sw.part_out;
+            sw.part_out = sw.part_in == part ? part2 : part;
+            if ((s2 = seg_sweep(ctx, dv, sw, true, false)) != HDG_OK) return s2;
+            if ((s2 = seg_givens(ctx, dv, sw.part_out, ctl, H, ldh, m, cs, sn, g, ldg, j, jmax, target)) != HDG_OK) return s2;
         }
         if ((s2 = seg_backsolve(ctx, dv, ctl, H, ldh, m, g, ldg, y)) != HDG_OK) return s2;
-        return seg_multiaxpy(ctx, dv, Z, ld, m, y, ldg, 1.0, x, ctl, true);
+        return seg_update(ctx, dv, Z, ld, y, ldg, x, ctl);
     };
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;

@@ -25,17 +25,53 @@ struct BatchCtl {
     double beta, est, pad2, pad3;
 };
 
+// One block of the face operator: 256 >> lteam faces of instance inst from instance-local face f0,
+// 1 << lteam threads a face.
+struct FaceBlk {
+    int32_t inst, f0, lteam, pad;
+};
+
+// Threads of a face with blocks of edge nb (log2): 8, 16 or 32, at least nb and half its S*nb columns
+// (the block's gathered x then fits 512 doubles), so that a thread has at most 14 entries.
+inline int batch_team(int nb, int S) {
+    int l = 3;
+    while (l < 5 && ((1 << l) < 4 * nb || 2 << l < S * nb)) ++l;
+    return l;
+}
+
+// Entries of a reduction chunk. 96 instances of 270,000 unknowns in all give 580 blocks.
+constexpr int SEG_CHUNK = 512;
+
+// One Gram-Schmidt sweep (k_seg_sweep): w against the J basis vectors V. part_in: the sweep's
+// coefficients as the partials of the sweep before; col: this step's Hessenberg column (stride
+// ld_col per instance), set or added to. The index arrays are the launcher's to fill in.
+struct SegSweep {
+    const double* V;
+    size_t ldv;
+    int J;
+    double* w;
+    const double* part_in;
+    double* part_out;
+    double* col;
+    int ld_col, add;
+    const BatchCtl* ctl;
+    const int32_t *blk_inst, *ib0, *ib1;
+    const int64_t *blk_lo, *blk_hi;
+    int nblk;
+};
+
 struct BatchDev {
     InstDesc* desc = nullptr;
     int32_t* eid = nullptr;         // [total_ne] instance of each element
     int32_t* fid = nullptr;         // [total_nf]
+    FaceBlk* fblk = nullptr;        // [nfblk] blocks of the face operator
     int32_t* dof_inst = nullptr;    // [total_dof]
     int32_t* blk_inst = nullptr;    // [nblk] reduction chunks (never straddle instances)
     int64_t* blk_lo = nullptr;
     int64_t* blk_hi = nullptr;
     int32_t* ib0 = nullptr;         // [n_inst] first / one-past-last chunk of each instance
     int32_t* ib1 = nullptr;
-    int n_inst = 0, nblk = 0;
+    int n_inst = 0, nblk = 0, nfblk = 0;
     int64_t total_ne = 0, total_nf = 0, total_dof = 0;
     size_t max_cond_lds = 0, max_rec_lds = 0;
     int max_nb = 0, max_snb = 0, max_R = 0;
@@ -78,15 +114,13 @@ hdg_status batch_launch_assemble(hdg_ctx ctx, const BatchDev& b, const int32_t* 
                                  const double* Kbar, const double* rbar, double* K64, float* K32, int32_t* nbr,
                                  double* r);
 hdg_status batch_launch_face(hdg_ctx ctx, const BatchDev& b, const void* M1, bool fp32, const int32_t* nbr,
-                             bool bj_only, const double* x, double* out, double s0, const double* X, double a0,
-                             const BatchCtl* ctl);
+                             bool bj_only, double* x, double* out, double s0, const double* X, double a0,
+                             const double* denom, int ld_denom, const BatchCtl* ctl);
 hdg_status batch_launch_bj(hdg_ctx ctx, const BatchDev& b, const double* K64, double* B64, float* B32, int* bad);
-hdg_status seg_multidot(hdg_ctx ctx, const BatchDev& b, const double* V, size_t ldv, int J, const double* w,
-                        double* part, const BatchCtl* ctl);
-hdg_status seg_reduce(hdg_ctx ctx, const BatchDev& b, const double* part, int J, double* out, int ldo, bool add,
-                      double* copy_to, int ldc, const BatchCtl* ctl);
-hdg_status seg_multiaxpy(hdg_ctx ctx, const BatchDev& b, const double* V, size_t ldv, int J, const double* h,
-                         int ldh, double sign, double* w, const BatchCtl* ctl, bool use_kdev);
+hdg_status seg_sweep(hdg_ctx ctx, const BatchDev& b, SegSweep a, bool axpy, bool dot);
+hdg_status seg_reduce(hdg_ctx ctx, const BatchDev& b, const double* part, double* out, int ldo);
+hdg_status seg_update(hdg_ctx ctx, const BatchDev& b, const double* Z, size_t ldz, const double* y, int ldy, double* x,
+                      const BatchCtl* ctl);
 hdg_status seg_sumsq(hdg_ctx ctx, const BatchDev& b, const double* w, double* part, const BatchCtl* ctl);
 hdg_status seg_scale(hdg_ctx ctx, const BatchDev& b, double* v, const double* denom, int ld_denom,
                      const BatchCtl* ctl);

@@ -11,6 +11,7 @@
 #include <cmath>
 
 #include "hdg_batch.hpp"
+#include "wave_ops.hpp"
 
 namespace {
 
@@ -203,40 +204,71 @@ __global__ __launch_bounds__(BS) void k_batch_assemble(const InstDesc* __restric
 // ---- face-block operator -----------------------------------------------------------------------
 // u_f = sum_s M1[f][s] x_{nbr[f][s]} (or the block-diagonal product when bj_only), then
 // out_f = s0 u_f + a0 X_f (X may be null); faces of finished instances are skipped.
+// bj_only with denom: x_f is first divided by its instance's denom[inst * ld_denom] and written back
+// (the normalisation of a new basis vector, which only its own face reads here).
+// Bound by latency at these sizes (a face is 0.1 to 1.4 KB of FP32 blocks): a block's faces are of
+// one instance, whose descriptor then comes by scalar loads, a face has the fewest threads that
+// leave each a handful of entries (batch_team), so that fewer waves pass through the chain of
+// dependent loads, and the first FU block entries of every thread are on their way before the
+// neighbour numbers and x are gathered (96 instances: 9.3 us a launch; 32 threads for every face and
+// a descriptor looked up per face 16.8).
 template <typename T>
 __global__ __launch_bounds__(BS) void k_batch_face(const InstDesc* __restrict__ desc,
-                                                   const int32_t* __restrict__ fid, int64_t total_nf,
+                                                   const FaceBlk* __restrict__ fblk,
                                                    const T* __restrict__ M1, const int32_t* __restrict__ nbr,
-                                                   int bj_only, const double* __restrict__ x, double* out,
+                                                   int bj_only, double* x, double* out,
                                                    double s0, const double* X, double a0,
-                                                   const BatchCtl* ctl) {
-    constexpr int TEAM = 32, FPB = BS / TEAM;
-    extern __shared__ double sm[];
-    const int team = threadIdx.x / TEAM, t = threadIdx.x % TEAM;
-    const int64_t g = (int64_t)blockIdx.x * FPB + team;
-    const bool valid = g < total_nf;
-    int inst = valid ? fid[g] : 0;
+                                                   const double* denom, int ld_denom, const BatchCtl* ctl) {
+    constexpr int FU = 8;
+    __shared__ double sm[512], red[BS];
+    const FaceBlk fb = fblk[blockIdx.x];
+    const int inst = fb.inst;
+    if (ctl && ctl[inst].done) return;
     const InstDesc& q = desc[inst];
-    const bool live = valid && !(ctl && ctl[inst].done);
-    const int nb = q.nb, S = bj_only ? 1 : q.S;
-    const int64_t f = g - q.f0;
-    double* xs = sm + (size_t)team * 64;       // S*nb <= 64 per face
-    double* red = sm + (size_t)FPB * 64;
-    int Seff = S;
-    if (live && !bj_only && S > q.L && nbr[q.nbr_off + f * S + q.L] < 0) Seff = q.L;
-    const int ncols = Seff * nb;
-    if (live)
-        for (int i = t; i < ncols; i += TEAM) {
-            const int s = i / nb, c = i - s * nb;
-            const int64_t gg = bj_only ? f : nbr[q.nbr_off + f * S + s];
-            xs[i] = x[q.vec_off + gg * nb + c];
-        }
-    __syncthreads();
+    const int lteam = fb.lteam, TEAM = 1 << lteam, team = threadIdx.x >> lteam, t = threadIdx.x & (TEAM - 1);
+    const int nb = q.nb, S = bj_only ? 1 : q.S, L = q.L, cols = S * nb;
+    const int fl = fb.f0 + team;
+    const bool live = fl < q.nf;
+    const int64_t f = live ? fl : q.nf - 1;
+    double* xs = sm + team * q.S * nb;         // BS / TEAM faces of S*nb <= 2 TEAM entries
     const int G = TEAM / nb, grp = t / nb, row = t - grp * nb;
+    const bool mine = grp < G;
+    const T* Mf = M1 + (bj_only ? q.binv_off : q.K_off) + f * cols * nb;
+    T a[FU];
+#pragma unroll
+    for (int u = 0; u < FU; ++u) {
+        const int k = grp + u * G;
+        a[u] = (mine && k < cols) ? Mf[k * nb + row] : (T)0;        // an empty slot's entries are not used
+    }
+    // a boundary face's empty slots are its last: entries past ncols are neither gathered nor used
+    bool empty = false;
+    for (int i = t; i < cols; i += TEAM) {
+        const int s = i / nb, c = i - s * nb;
+        const int64_t gg = bj_only ? f : nbr[q.nbr_off + f * S + s];
+        double v = 0.0;
+        if (gg >= 0) {
+            double* xp = x + q.vec_off + gg * nb + c;
+            v = *xp;
+            if (denom) {
+                v /= denom[(size_t)inst * ld_denom];
+                if (live) *xp = v;
+            }
+        } else {
+            empty = empty || s >= L;
+        }
+        xs[i] = v;
+    }
+    const uint64_t any = __ballot(empty) >> (threadIdx.x & 63 & ~(TEAM - 1)) & ((TEAM < 64 ? 1ull << TEAM : 0ull) - 1);
+    const int ncols = any ? L * nb : cols;
+    __syncthreads();
     double acc = 0.0;
-    if (live && grp < G) {
-        const T* Mf = M1 + (bj_only ? q.binv_off : q.K_off) + f * S * nb * nb;
-        for (int k = grp; k < ncols; k += G) acc += (double)Mf[(int64_t)k * nb + row] * xs[k];
+    if (mine) {
+#pragma unroll
+        for (int u = 0; u < FU; ++u) {
+            const int k = grp + u * G;
+            if (k < ncols) acc += (double)a[u] * xs[k];
+        }
+        for (int k = grp + FU * G; k < ncols; k += G) acc += (double)Mf[k * nb + row] * xs[k];
     }
     red[threadIdx.x] = acc;
     __syncthreads();
@@ -310,69 +342,138 @@ __global__ __launch_bounds__(BS) void k_batch_bj(const InstDesc* __restrict__ de
 }
 
 // ---- segmented Krylov kernels -------------------------------------------------------------------
-// Block b covers entries [blk_lo[b], blk_hi[b]) of instance blk_inst[b] (chunks never straddle
-// two instances). part[i * nblk + b].
-__global__ __launch_bounds__(BS) void k_seg_multidot(const int32_t* __restrict__ blk_inst,
-                                                     const int64_t* __restrict__ blk_lo, const int64_t* __restrict__ blk_hi,
-                                                     const double* __restrict__ V, size_t ldv, int J,
-                                                     const double* __restrict__ w, double* part, int nblk,
-                                                     const BatchCtl* ctl) {
-    __shared__ double red[64][BS / 64];
-    const int b = blockIdx.x;
-    if (ctl && ctl[blk_inst[b]].done) return;
-    const int64_t k0 = blk_lo[b], k1 = blk_hi[b];
+// Block b covers entries [blk_lo[b], blk_hi[b]) of instance blk_inst[b] (at most SEG_CHUNK; chunks
+// never straddle two instances). part[i * nblk + b].
+// One Gram-Schmidt sweep over an instance's basis: the coefficients h_i = sum_b part_in[i][b] of the
+// sweep before (AXPY; every block of the instance adds them up in the same order, its first block
+// puts them into the Hessenberg column), w -= V h, then the partial inner products V^T w (DOT) or
+// ||w||^2. A wave takes four columns at a time with all their loads in flight; a sweep by one column
+// after another, with reductions in kernels of their own, took 31 + 4 + 7 us a sweep for 96
+// instances (270,000 unknowns, up to 30 columns, averages over cycles in which ever fewer are
+// active); this one 7 (DOT), 11 (both) and 8 us (AXPY).
+constexpr int SEG_U = SEG_CHUNK / 64, SEG_C = 4;
+template <bool AXPY, bool DOT>
+__global__ __launch_bounds__(BS) void k_seg_sweep(SegSweep a) {
+    __shared__ double hs[AXPY ? 200 : 1], ws[SEG_CHUNK], red[BS / 64];
+    const int b = blockIdx.x, inst = a.blk_inst[b];
+    if (a.ctl[inst].done) return;
+    const int64_t k0 = a.blk_lo[b];
+    const int len = (int)(a.blk_hi[b] - k0), J = a.J, nblk = a.nblk;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int i0 = 0; i0 < J; i0 += 64) {
-        const int ni = (J - i0) < 64 ? (J - i0) : 64;
-        for (int ii = 0; ii < ni; ++ii) {
-            const double* v = V + (size_t)(i0 + ii) * ldv;
-            double acc = 0.0;
-            for (int64_t k = k0 + threadIdx.x; k < k1; k += BS) acc += v[k] * w[k];
-            acc = wave_sum(acc);
-            if (lane == 0) red[ii][wave] = acc;
+    const double* V = a.V + k0;
+    double* w = a.w + k0;
+    if constexpr (AXPY) {
+        const int b0 = a.ib0[inst], b1 = a.ib1[inst];
+        for (int i = wave * SEG_C; i < J; i += (BS / 64) * SEG_C) {
+            double s[SEG_C] = {};
+            for (int q = b0 + lane; q < b1; q += 64)
+#pragma unroll
+                for (int c = 0; c < SEG_C; ++c) s[c] += a.part_in[(size_t)(i + c < J ? i + c : i) * nblk + q];
+#pragma unroll
+            for (int c = 0; c < SEG_C; ++c) {
+                const double h = wave_ops::wave_sum_all(s[c]);
+                if (lane == 0 && i + c < J) hs[i + c] = h;
+            }
         }
         __syncthreads();
-        if (threadIdx.x < ni) {
-            double s = 0.0;
-            for (int q = 0; q < BS / 64; ++q) s += red[threadIdx.x][q];
-            part[(size_t)(i0 + threadIdx.x) * nblk + b] = s;
+        if (b == b0) {
+            double* col = a.col + (size_t)inst * a.ld_col;
+            for (int i = threadIdx.x; i < J; i += BS) col[i] = a.add ? col[i] + hs[i] : hs[i];
         }
+        constexpr int E = SEG_CHUNK / BS;
+        double acc[E] = {};
+        for (int i = 0; i < J; i += 8) {
+            double v[8][E];
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+#pragma unroll
+                for (int u = 0; u < E; ++u) {
+                    const int k = threadIdx.x + u * BS;
+                    v[c][u] = V[(size_t)(i + c < J ? i + c : i) * a.ldv + (k < len ? k : 0)];
+                }
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+#pragma unroll
+                for (int u = 0; u < E; ++u)
+                    if (i + c < J) acc[u] += v[c][u] * hs[i + c];
+        }
+        double ss = 0.0;
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            const int k = threadIdx.x + u * BS;
+            const double r = k < len ? w[k] - acc[u] : 0.0;
+            if (k < len) w[k] = r;
+            if constexpr (DOT) ws[k] = r;
+            ss += r * r;
+        }
+        if constexpr (!DOT) {
+            ss = wave_ops::wave_sum_all(ss);
+            if (lane == 0) red[wave] = ss;
+            __syncthreads();
+            if (threadIdx.x == 0) a.part_out[b] = (red[0] + red[1]) + (red[2] + red[3]);
+            return;
+        }
+    } else {
+        for (int k = threadIdx.x; k < SEG_CHUNK; k += BS) ws[k] = k < len ? w[k] : 0.0;
+    }
+    if constexpr (DOT) {
         __syncthreads();
+        double wr[SEG_U];
+#pragma unroll
+        for (int u = 0; u < SEG_U; ++u) wr[u] = ws[lane + 64 * u];
+        for (int i = wave * SEG_C; i < J; i += (BS / 64) * SEG_C) {
+            double v[SEG_C][SEG_U];
+#pragma unroll
+            for (int c = 0; c < SEG_C; ++c)
+#pragma unroll
+                for (int u = 0; u < SEG_U; ++u) {
+                    const int k = lane + 64 * u;
+                    v[c][u] = V[(size_t)(i + c < J ? i + c : i) * a.ldv + (k < len ? k : 0)];
+                }
+#pragma unroll
+            for (int c = 0; c < SEG_C; ++c) {
+                double s = 0.0;
+#pragma unroll
+                for (int u = 0; u < SEG_U; ++u)
+                    if (lane + 64 * u < len) s += v[c][u] * wr[u];
+                s = wave_ops::wave_sum_all(s);
+                if (lane == 0 && i + c < J) a.part_out[(size_t)(i + c) * nblk + b] = s;
+            }
+        }
     }
 }
 
-// out[inst * ldo + i] (= or +=) sum of part[i][b] over the instance's blocks; one wave per (inst, i)
+// out[inst * ldo] = sum of part[b] over the instance's blocks; one wave per instance
 __global__ void k_seg_reduce(const int32_t* __restrict__ ib0, const int32_t* __restrict__ ib1, int n_inst,
-                             const double* __restrict__ part, int J, int nblk, double* out, int ldo, int add,
-                             double* copy_to, int ldc, const BatchCtl* ctl) {
-    const int w = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+                             const double* __restrict__ part, double* out, int ldo) {
+    const int inst = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (w >= n_inst * J) return;
-    const int inst = w / J, i = w - inst * J;
-    if (ctl && ctl[inst].done) return;
+    if (inst >= n_inst) return;
     double s = 0.0;
-    for (int b = ib0[inst] + lane; b < ib1[inst]; b += 64) s += part[(size_t)i * nblk + b];
+    for (int b = ib0[inst] + lane; b < ib1[inst]; b += 64) s += part[b];
     s = wave_sum(s);
-    if (lane == 0) {
-        if (copy_to) copy_to[(size_t)inst * ldc + i] = s;
-        if (add) out[(size_t)inst * ldo + i] += s;
-        else out[(size_t)inst * ldo + i] = s;
-    }
+    if (lane == 0) out[(size_t)inst * ldo] = s;
 }
 
-// w[k] += sign * sum_{i<J} V[i][k] h[inst(k)][i], J = Jdev[inst] when given
-__global__ __launch_bounds__(BS) void k_seg_multiaxpy(const int32_t* __restrict__ dof_inst, const double* V,
-                                                      size_t ldv, int J, const double* h, int ldh, double sign,
-                                                      double* w, size_t n, const BatchCtl* ctl, int use_kdev) {
+// x[k] += sum_{i<k_inst} Z[i][k] y[inst(k)][i] with k_inst the instance's steps this cycle
+__global__ __launch_bounds__(BS) void k_seg_update(const int32_t* __restrict__ dof_inst, const double* __restrict__ Z,
+                                                   size_t ldz, const double* __restrict__ y, int ldy, double* x,
+                                                   size_t n, const BatchCtl* ctl) {
     const size_t k = (size_t)blockIdx.x * BS + threadIdx.x;
     if (k >= n) return;
     const int inst = dof_inst[k];
-    if (ctl && !use_kdev && ctl[inst].done) return;
-    const int JJ = use_kdev ? ctl[inst].k : J;
-    const double* hh = h + (size_t)inst * ldh;
+    const int J = ctl[inst].k;
+    const double* yy = y + (size_t)inst * ldy;
     double acc = 0.0;
-    for (int i = 0; i < JJ; ++i) acc += V[(size_t)i * ldv + k] * hh[i];
-    w[k] += sign * acc;
+    for (int i = 0; i < J; i += 8) {
+        double z[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) z[c] = Z[(size_t)(i + c < J ? i + c : i) * ldz + k];
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+            if (i + c < J) acc += z[c] * yy[i + c];
+    }
+    x[k] += acc;
 }
 
 __global__ __launch_bounds__(BS) void k_seg_sumsq(const int32_t* __restrict__ blk_inst,
@@ -420,63 +521,93 @@ __global__ void k_seg_cycle_init(const int32_t* __restrict__ ib0, const int32_t*
     }
 }
 
-__global__ void k_seg_givens(const int32_t* __restrict__ ib0, const int32_t* __restrict__ ib1, int n_inst,
-                             const double* part, BatchCtl* ctl, double* H, int ldh, int mcols, double* cs,
-                             double* sn, double* g, int ldg, int j, int jmax, const double* target) {
-    const int inst = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (inst >= n_inst) return;
+// One wave per instance: ||w|| from the sweep's partials, the earlier rotations on the new column (the
+// column and the rotations staged in LDS: the chain of dependent updates then waits on no memory),
+// the new rotation and the residual estimate.
+__global__ __launch_bounds__(64) void k_seg_givens(const int32_t* __restrict__ ib0, const int32_t* __restrict__ ib1,
+                                                   const double* part, BatchCtl* ctl, double* H, int ldh, int mcols,
+                                                   double* cs, double* sn, double* g, int ldg, int j, int jmax,
+                                                   const double* target) {
+    __shared__ double sc[201], cc_s[200], ss_s[200];
+    const int inst = blockIdx.x, lane = threadIdx.x;
     BatchCtl& c = ctl[inst];
     if (c.done) return;
-    double s = 0.0;
-    for (int b = ib0[inst] + lane; b < ib1[inst]; b += 64) s += part[b];
-    s = wave_sum(s);
-    if (lane != 0) return;
-    const double hn = sqrt(s);
-    double* Hi = H + (size_t)inst * ldh * mcols;
-    double* col = Hi + (size_t)j * ldh;
+    double* col = H + (size_t)inst * ldh * mcols + (size_t)j * ldh;
     double* csi = cs + (size_t)inst * ldg;
     double* sni = sn + (size_t)inst * ldg;
     double* gi = g + (size_t)inst * ldg;
-    col[j + 1] = hn;
-    for (int i = 0; i < j; ++i) {
-        const double t = csi[i] * col[i] + sni[i] * col[i + 1];
-        col[i + 1] = -sni[i] * col[i] + csi[i] * col[i + 1];
-        col[i] = t;
+    const double gj = gi[j], tgt = target[inst];
+    for (int i = lane; i <= j; i += 64) sc[i] = col[i];
+    for (int i = lane; i < j; i += 64) {
+        cc_s[i] = csi[i];
+        ss_s[i] = sni[i];
     }
-    const double hjj = col[j];
-    double cc = 1.0, sg = 0.0;
-    if (hn != 0.0) {
-        const double r = hypot(hjj, hn);
-        cc = hjj / r;
-        sg = hn / r;
+    double s = 0.0;
+    for (int b = ib0[inst] + lane; b < ib1[inst]; b += 64) s += part[b];
+    s = wave_sum(s);
+    __syncthreads();
+    const double hn = sqrt(s);
+    if (lane == 0) {
+        double h = sc[0];
+        for (int i = 0; i < j; ++i) {
+            const double nx = sc[i + 1];
+            sc[i] = cc_s[i] * h + ss_s[i] * nx;
+            h = -ss_s[i] * h + cc_s[i] * nx;
+        }
+        double ct = 1.0, st = 0.0;
+        if (hn != 0.0) {
+            const double r = hypot(h, hn);
+            ct = h / r;
+            st = hn / r;
+        }
+        csi[j] = ct;
+        sni[j] = st;
+        sc[j] = ct * h + st * hn;
+        col[j + 1] = hn;
+        gi[j + 1] = -st * gj;
+        gi[j] = ct * gj;
+        const double est = fabs(-st * gj);
+        c.est = est;
+        c.k = j + 1;
+        if (!isfinite(est)) c.nonfinite = 1;
+        if (est <= tgt || hn == 0.0 || j + 1 >= jmax || !isfinite(est)) c.done = 1;
     }
-    csi[j] = cc;
-    sni[j] = sg;
-    col[j] = cc * hjj + sg * hn;
-    const double gj = gi[j];
-    gi[j + 1] = -sg * gj;
-    gi[j] = cc * gj;
-    const double est = fabs(gi[j + 1]);
-    c.est = est;
-    c.k = j + 1;
-    if (!isfinite(est)) c.nonfinite = 1;
-    if (est <= target[inst] || hn == 0.0 || j + 1 >= jmax || !isfinite(est)) c.done = 1;
+    __syncthreads();
+    for (int i = lane; i <= j; i += 64) col[i] = sc[i];
 }
 
-__global__ void k_seg_backsolve(int n_inst, const BatchCtl* ctl, const double* H, int ldh, int mcols,
-                                const double* g, int ldg, double* y) {
-    const int inst = blockIdx.x * blockDim.x + threadIdx.x;
-    if (inst >= n_inst) return;
+// R y = g by columns, one wave per instance: the unknowns still to come stay in LDS and the next
+// column of R is loaded while the current one is applied.
+__global__ __launch_bounds__(64) void k_seg_backsolve(const BatchCtl* ctl, const double* H, int ldh, int mcols,
+                                                      const double* g, int ldg, double* y) {
+    __shared__ double ys[201];
+    const int inst = blockIdx.x, lane = threadIdx.x;
     const int k = ctl[inst].k;
     const double* Hi = H + (size_t)inst * ldh * mcols;
-    const double* gi = g + (size_t)inst * ldg;
-    double* yi = y + (size_t)inst * ldg;
-    for (int i = k - 1; i >= 0; --i) {
-        double s = gi[i];
-        for (int c = i + 1; c < k; ++c) s -= Hi[(size_t)c * ldh + i] * yi[c];
-        yi[i] = s / Hi[(size_t)i * ldh + i];
+    for (int i = lane; i < k; i += 64) ys[i] = g[(size_t)inst * ldg + i];
+    __syncthreads();
+    double nx[4];
+    auto load = [&](int c) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) nx[u] = (c >= 0 && lane + 64 * u <= c) ? Hi[(size_t)c * ldh + lane + 64 * u] : 0.0;
+    };
+    load(k - 1);
+    for (int c = k - 1; c >= 0; --c) {
+        double r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) r[u] = nx[u];
+        load(c - 1);
+        const int du = c >> 6;
+        const double rd = du == 0 ? r[0] : du == 1 ? r[1] : du == 2 ? r[2] : r[3];
+        const double yc = ys[c] / wave_ops::read_lane(rd, c & 63);
+        __syncthreads();
+        if (lane == 0) ys[c] = yc;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (lane + 64 * u < c) ys[lane + 64 * u] -= r[u] * yc;
+        __syncthreads();
     }
+    for (int i = lane; i < k; i += 64) y[(size_t)inst * ldg + i] = ys[i];
 }
 
 // ---- recovery ------------------------------------------------------------------------------------
@@ -566,17 +697,14 @@ hdg_status batch_launch_assemble(hdg_ctx ctx, const BatchDev& b, const int32_t* 
 }
 
 hdg_status batch_launch_face(hdg_ctx ctx, const BatchDev& b, const void* M1, bool fp32, const int32_t* nbr,
-                             bool bj_only, const double* x, double* out, double s0, const double* X, double a0,
-                             const BatchCtl* ctl) {
-    const int fpb = BS / 32;
-    const int grid = (int)((b.total_nf + fpb - 1) / fpb);
-    const size_t lds = sizeof(double) * ((size_t)fpb * 64 + BS);
+                             bool bj_only, double* x, double* out, double s0, const double* X, double a0,
+                             const double* denom, int ld_denom, const BatchCtl* ctl) {
     if (fp32)
-        hipLaunchKernelGGL(k_batch_face<float>, dim3(grid), dim3(BS), lds, ctx->stream, b.desc, b.fid, b.total_nf,
-                           (const float*)M1, nbr, bj_only ? 1 : 0, x, out, s0, X, a0, ctl);
+        hipLaunchKernelGGL(k_batch_face<float>, dim3(b.nfblk), dim3(BS), 0, ctx->stream, b.desc, b.fblk, (const float*)M1,
+                           nbr, bj_only ? 1 : 0, x, out, s0, X, a0, denom, ld_denom, ctl);
     else
-        hipLaunchKernelGGL(k_batch_face<double>, dim3(grid), dim3(BS), lds, ctx->stream, b.desc, b.fid, b.total_nf,
-                           (const double*)M1, nbr, bj_only ? 1 : 0, x, out, s0, X, a0, ctl);
+        hipLaunchKernelGGL(k_batch_face<double>, dim3(b.nfblk), dim3(BS), 0, ctx->stream, b.desc, b.fblk,
+                           (const double*)M1, nbr, bj_only ? 1 : 0, x, out, s0, X, a0, denom, ld_denom, ctl);
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }
@@ -589,29 +717,33 @@ hdg_status batch_launch_bj(hdg_ctx ctx, const BatchDev& b, const double* K64, do
     return HDG_OK;
 }
 
-hdg_status seg_multidot(hdg_ctx ctx, const BatchDev& b, const double* V, size_t ldv, int J, const double* w,
-                        double* part, const BatchCtl* ctl) {
-    if (J <= 0) return HDG_OK;
-    hipLaunchKernelGGL(k_seg_multidot, dim3(b.nblk), dim3(BS), 0, ctx->stream, b.blk_inst, b.blk_lo, b.blk_hi, V, ldv,
-                       J, w, part, b.nblk, ctl);
+hdg_status seg_sweep(hdg_ctx ctx, const BatchDev& b, SegSweep a, bool axpy, bool dot) {
+    a.blk_inst = b.blk_inst;
+    a.blk_lo = b.blk_lo;
+    a.blk_hi = b.blk_hi;
+    a.ib0 = b.ib0;
+    a.ib1 = b.ib1;
+    a.nblk = b.nblk;
+    const void* k = !axpy ? (const void*)k_seg_sweep<false, true>
+                    : dot ? (const void*)k_seg_sweep<true, true>
+                          : (const void*)k_seg_sweep<true, false>;
+    void* args[] = {(void*)&a};
+    HDG_HIP_CHECK(ctx, hipLaunchKernel(k, dim3(b.nblk), dim3(BS), args, 0, ctx->stream));
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }
 
-hdg_status seg_reduce(hdg_ctx ctx, const BatchDev& b, const double* part, int J, double* out, int ldo, bool add,
-                      double* copy_to, int ldc, const BatchCtl* ctl) {
-    if (J <= 0) return HDG_OK;
-    const int waves = b.n_inst * J;
-    hipLaunchKernelGGL(k_seg_reduce, dim3(div_up(waves, 4)), dim3(256), 0, ctx->stream, b.ib0, b.ib1, b.n_inst, part,
-                       J, b.nblk, out, ldo, add ? 1 : 0, copy_to, ldc, ctl);
+hdg_status seg_reduce(hdg_ctx ctx, const BatchDev& b, const double* part, double* out, int ldo) {
+    hipLaunchKernelGGL(k_seg_reduce, dim3(div_up(b.n_inst, 4)), dim3(256), 0, ctx->stream, b.ib0, b.ib1, b.n_inst, part,
+                       out, ldo);
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }
 
-hdg_status seg_multiaxpy(hdg_ctx ctx, const BatchDev& b, const double* V, size_t ldv, int J, const double* h,
-                         int ldh, double sign, double* w, const BatchCtl* ctl, bool use_kdev) {
-    hipLaunchKernelGGL(k_seg_multiaxpy, dim3(div_up((long long)b.total_dof, BS)), dim3(BS), 0, ctx->stream,
-                       b.dof_inst, V, ldv, J, h, ldh, sign, w, (size_t)b.total_dof, ctl, use_kdev ? 1 : 0);
+hdg_status seg_update(hdg_ctx ctx, const BatchDev& b, const double* Z, size_t ldz, const double* y, int ldy, double* x,
+                      const BatchCtl* ctl) {
+    hipLaunchKernelGGL(k_seg_update, dim3(div_up((long long)b.total_dof, BS)), dim3(BS), 0, ctx->stream, b.dof_inst, Z,
+                       ldz, y, ldy, x, (size_t)b.total_dof, ctl);
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }
@@ -641,16 +773,14 @@ hdg_status seg_cycle_init(hdg_ctx ctx, const BatchDev& b, const double* part, Ba
 
 hdg_status seg_givens(hdg_ctx ctx, const BatchDev& b, const double* part, BatchCtl* ctl, double* H, int ldh, int mcols,
                       double* cs, double* sn, double* g, int ldg, int j, int jmax, const double* target) {
-    hipLaunchKernelGGL(k_seg_givens, dim3(div_up(b.n_inst, 4)), dim3(256), 0, ctx->stream, b.ib0, b.ib1, b.n_inst,
-                       part, ctl, H, ldh, mcols, cs, sn, g, ldg, j, jmax, target);
+    hipLaunchKernelGGL(k_seg_givens, dim3(b.n_inst), dim3(64), 0, ctx->stream, b.ib0, b.ib1, part, ctl, H, ldh, mcols, cs, sn, g, ldg, j, jmax, target);
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }
 
 hdg_status seg_backsolve(hdg_ctx ctx, const BatchDev& b, const BatchCtl* ctl, const double* H, int ldh, int mcols,
                          const double* g, int ldg, double* y) {
-    hipLaunchKernelGGL(k_seg_backsolve, dim3(div_up(b.n_inst, 64)), dim3(64), 0, ctx->stream, b.n_inst, ctl, H, ldh,
-                       mcols, g, ldg, y);
+    hipLaunchKernelGGL(k_seg_backsolve, dim3(b.n_inst), dim3(64), 0, ctx->stream, ctl, H, ldh, mcols, g, ldg, y);
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }
