@@ -5,8 +5,8 @@
 // workgroup: its quadrature geometry and state are staged in LDS, the state is evaluated at
 // the quadrature points (the Phi/Psi products of Section 4.1 as per-point sums), the flux
 // and its derivatives are formed per point, and every output entry is one sum over the
-// volume or face points. q is derived from the q-equation (M q_d + B_d u + C_d uhat = 0),
-// so r_q = 0.
+// volume or face points, taken as 16x16 tiles on the FP64 matrix cores. q is derived from the
+// q-equation (M q_d + B_d u + C_d uhat = 0), so r_q = 0.
 //
 // Residual rows (the sign of the trace rows as everywhere in the library), with the time
 // term of an implicit stage (c = 1/(a_ii dt), u_n, r_x; c = 0 and no r_x: steady):
@@ -14,11 +14,14 @@
 //   R_t[l,j] = -<fhat, psi_j>_l (interior face), <uhat - u_D, psi_j>_l (Dirichlet face)
 // and ru = -R_u, rt = -R_t; D..J are their derivatives with respect to q, u and uhat.
 #include "hdg_batch.hpp"
+#include "wave_ops.hpp"
 
 namespace {
 
 constexpr int EBS = 256;
-constexpr int TJ = 4;      // output columns per work item in the (i, j) sums
+using wave_ops::d4;
+using wave_ops::mma16s;
+using wave_ops::seq;
 
 // One element's inputs and outputs, every pointer already at that element (phi and psi:
 // the reference tables; uhat: the face values of the element's mesh, indexed by e2f).
@@ -45,6 +48,12 @@ struct ElemArgs {
     int* bad;
     int ne, P, PF, L, D, residual_only, keep_mass;
 };
+
+// Threads of an element's block: one wave where every phase has one tile of basis functions (no
+// barrier then waits on another wave, and a CU holds four times the elements; 14400 p = 1 quads:
+// 0.27 ms with four waves, 0.19 with one). P = 25 by one wave: 1.3 ms for 16384 quads, by two 0.87,
+// by four 0.70.
+inline int elem_threads(int P) { return P <= 16 ? 64 : EBS; }
 
 // LDS offsets (in doubles) of the element's staged arrays
 struct ElemLds {
@@ -87,10 +96,18 @@ __host__ __device__ inline ElemLds elem_lds(int P, int PF, int L, int D, int Qv,
 // v[d] for d < 3 without dynamic indexing (which would put v in scratch memory)
 __device__ __forceinline__ double sel3(const double (&v)[3], int d) { return d == 0 ? v[0] : d == 1 ? v[1] : v[2]; }
 
+// Bound by the matrix-core tiles and by the element's arrays (each read and written once); every sum is
+// an mma16 tile with its operands in LDS, the tiles shared out over the four waves, where a thread per
+// entry spent two LDS loads on each multiply-add. Tiles are 16 wide, so P = 25 works at 61% of its
+// products. 16384 Burgers p = 4 quads, Jacobian with kept mass matrices: 0.87 ms by entries, 0.58 so
+// (1.7 TB/s; the copies to LDS alone 0.15 ms, the rest matrix-core and vector instructions in near
+// equal parts); 14400 p = 1 quads 0.26 and 0.16 ms.
+template <int D>
 __device__ __forceinline__ void element_body(const ElemView& a, double* sm) {
     const int e = a.eid;
-    const int tid = threadIdx.x;
-    const int P = a.P, PF = a.PF, L = a.L, D = a.Dm, Qv = a.Qv, Qf = a.Qf;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), BS = blockDim.x, NW = BS >> 6;
+    const int P = a.P, PF = a.PF, L = a.L, Qv = a.Qv, Qf = a.Qf;
     const int nt = L * PF;
     const ElemLds o = elem_lds(P, PF, L, D, Qv, Qf);
     double *phi = sm + o.phi, *dphi = sm + o.dphi, *wdet = sm + o.wdet, *phif = sm + o.phif, *psi = sm + o.psi;
@@ -99,52 +116,44 @@ __device__ __forceinline__ void element_body(const ElemView& a, double* sm) {
     double *Mm = sm + o.M, *t = sm + o.t, *q = sm + o.q, *uq = sm + o.uq, *qq = sm + o.qq, *uf = sm + o.uf;
     double *qf = sm + o.qf, *uhf = sm + o.uhf, *wF = sm + o.wF, *wFu = sm + o.wFu, *fhat = sm + o.fhat, *Z = sm + o.Z;
 
-    // 1. stage geometry, reference tables and state
-    for (int k = tid; k < Qv * P; k += EBS) phi[k] = a.phi[k];
-    for (int k = tid; k < Qv * P * D; k += EBS) dphi[k] = a.dphix[k];
-    for (int k = tid; k < Qv; k += EBS) {
-        wdet[k] = a.wdet[k];
-        src[k] = a.src[k];
-    }
-    for (int k = tid; k < L * Qf * P; k += EBS) phif[k] = a.phif[k];
-    for (int k = tid; k < Qf * PF; k += EBS) psi[k] = a.psi[k];
-    for (int k = tid; k < L * Qf * D; k += EBS) ndA[k] = a.ndA[k];
-    for (int k = tid; k < L * Qf; k += EBS) {
-        dA[k] = a.dA[k];
-        uD[k] = a.uD[k];
-    }
+    // 1. stage geometry, reference tables and state: every copy in flight at once
     const double cdt = a.c;
-    for (int k = tid; k < P; k += EBS) {
-        u[k] = a.u[k];
-        up[k] = cdt != 0.0 ? a.u_prev[k] : 0.0;
-    }
-    for (int k = tid; k < nt; k += EBS) {
-        const int l = k / PF, j = k - l * PF;
-        uh[k] = a.uhat[(size_t)a.e2f[l] * PF + j];
-    }
+    const int LQf = L * Qf;
+    auto stage = [&](const double* g, double* dst, int n) { wave_ops::copy_to_lds(g, dst, 8 * n, wave, NW); };
+    stage(a.dphix, dphi, Qv * P * D);
+    stage(a.phif, phif, LQf * P);
+    if (a.keep_mass) stage(a.Minv, Mm, P * P);
+    stage(a.phi, phi, Qv * P);
+    stage(a.ndA, ndA, LQf * D);
+    stage(a.wdet, wdet, Qv);
+    stage(a.src, src, Qv);
+    stage(a.psi, psi, Qf * PF);
+    stage(a.dA, dA, LQf);
+    stage(a.uD, uD, LQf);
+    stage(a.u, u, P);
+    if (cdt != 0.0) stage(a.u_prev, up, P);
+    for (int l = wave; l < L; l += NW) wave_ops::copy_to_lds(a.uhat + (size_t)a.e2f[l] * PF, uh + l * PF, 8 * PF, 0, 1);
+    wave_ops::copies_done();
     __syncthreads();
 
     // 2. mass matrix and its inverse (Gauss-Jordan in place; M is SPD, no interchanges), or
     //    the inverse kept from an earlier evaluation on the same mesh (state-independent)
-    const int nJT = (P + TJ - 1) / TJ;    // column tiles of TJ entries: one row i per work item
-    if (a.keep_mass) {
-        for (int k = tid; k < P * P; k += EBS) Mm[k] = a.Minv[k];
-        __syncthreads();
-    } else {
-        for (int it = tid; it < P * nJT; it += EBS) {
-            const int i = it / nJT, j0 = (it - i * nJT) * TJ;
-            double acc[TJ] = {};
-            for (int x = 0; x < Qv; ++x) {
-                const double wi = wdet[x] * phi[x * P + i];
+    // tiles go round the waves: job counts them, NW is a power of two
+    int job = 0;
+    auto mine = [&]() { return (job++ & (NW - 1)) == wave; };
+    if (!a.keep_mass) {
+        for (int i0 = 0; i0 < P; i0 += 16)
+            for (int j0 = 0; j0 < P; j0 += 16) {
+                if (!mine()) continue;
+                const int i = i0 + l16 < P ? i0 + l16 : P - 1, j = j0 + l16 < P ? j0 + l16 : P - 1;
+                d4 acc = {};
+                mma16s<true, false>(Qv, seq(phi + i, P, wdet, 1), seq(phi + j, P), acc);
 #pragma unroll
-                for (int jj = 0; jj < TJ; ++jj)
-                    if (j0 + jj < P) acc[jj] += wi * phi[x * P + j0 + jj];
+                for (int r = 0; r < 4; ++r)
+                    if (i0 + 4 * r + lq < P && j0 + l16 < P) Mm[(i0 + 4 * r + lq) * P + j0 + l16] = acc[r];
             }
-#pragma unroll
-            for (int jj = 0; jj < TJ; ++jj)
-                if (j0 + jj < P) Mm[i * P + j0 + jj] = acc[jj];
-        }
         __syncthreads();
+        const int gi = tid >> 4, gj = tid & 15;
         for (int k = 0; k < P; ++k) {
             const double piv = Mm[k * P + k];
             if (!(piv > 0.0) || !isfinite(piv)) {
@@ -153,15 +162,14 @@ __device__ __forceinline__ void element_body(const ElemView& a, double* sm) {
             }
             const double rp = 1.0 / piv;
             // row k scaled (entry k becomes 1/piv), other rows updated with the old column k
-            for (int idx = tid; idx < P * P; idx += EBS) {
-                const int i = idx / P, j = idx - i * P;
+            for (int i = gi; i < P; i += BS / 16) {
                 if (i == k) continue;
                 const double f = Mm[i * P + k] * rp;
-                if (j == k) continue;
-                Mm[idx] -= f * Mm[k * P + j];
+                for (int j = gj; j < P; j += 16)
+                    if (j != k) Mm[i * P + j] -= f * Mm[k * P + j];
             }
             __syncthreads();
-            for (int idx = tid; idx < P; idx += EBS) {
+            for (int idx = tid; idx < P; idx += BS) {
                 if (idx != k) {
                     Mm[idx * P + k] = -Mm[idx * P + k] * rp;
                     Mm[k * P + idx] *= rp;
@@ -172,67 +180,90 @@ __device__ __forceinline__ void element_body(const ElemView& a, double* sm) {
         }
     }
 
-    // 3. u and uhat at the quadrature points
-    for (int k = tid; k < Qv; k += EBS) {
-        double s = 0.0, sp = 0.0;
-        for (int i = 0; i < P; ++i) {
-            s += phi[k * P + i] * u[i];
-            sp += phi[k * P + i] * up[i];
+    // 3. u and u_n (columns 0 and 1) at the volume points, u at the face points, uhat at the points
+    //    of every face (a column per face)
+    for (int vol = 1; vol >= 0; --vol) {
+        const int n = vol ? Qv : LQf;
+        for (int x0 = 0; x0 < n; x0 += 16) {
+            if (!mine()) continue;
+            const int x = x0 + l16 < n ? x0 + l16 : n - 1;
+            d4 acc = {};
+            mma16s<false, false>(P, seq((vol ? phi : phif) + x * P, 1), seq(l16 == 1 && cdt != 0.0 ? up : u, 1), acc);
+            double* dst = !vol ? uf : l16 == 0 ? uq : duq;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (x0 + 4 * r + lq < n && l16 <= vol) dst[x0 + 4 * r + lq] = acc[r];
         }
-        uq[k] = s;
-        duq[k] = s - sp;     // u - u_n at the point (time term)
     }
-    for (int k = tid; k < L * Qf; k += EBS) {
-        const int l = k / Qf, x = k - l * Qf;
-        double s = 0.0, h = 0.0;
-        for (int i = 0; i < P; ++i) s += phif[k * P + i] * u[i];
-        for (int j = 0; j < PF; ++j) h += psi[x * PF + j] * uh[l * PF + j];
-        uf[k] = s;
-        uhf[k] = h;
+    for (int x0 = 0; x0 < Qf; x0 += 16) {                // L <= 6 columns
+        if (!mine()) continue;
+        const int x = x0 + l16 < Qf ? x0 + l16 : Qf - 1, l = l16 < L ? l16 : L - 1;
+        d4 acc = {};
+        mma16s<false, false>(PF, seq(psi + x * PF, 1), seq(uh + l * PF, 1), acc);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (x0 + 4 * r + lq < Qf && l16 < L) uhf[l16 * Qf + x0 + 4 * r + lq] = acc[r];
     }
     __syncthreads();
 
-    // 4. q = -M^{-1} (B_d u + C_d uhat), with B_d u and C_d uhat summed over the points
-    for (int k = tid; k < D * P; k += EBS) {
-        const int d = k / P, i = k - d * P;
-        double s = 0.0;
-        for (int x = 0; x < Qv; ++x) s += wdet[x] * dphi[(x * P + i) * D + d] * uq[x];
-        for (int lx = 0; lx < L * Qf; ++lx) s -= ndA[lx * D + d] * phif[lx * P + i] * uhf[lx];
-        t[k] = s;
-    }
+    // 4. q = -M^{-1} (B_d u + C_d uhat): -B_d u in t, the face sums in q, both then one operand of the
+    //    product with M^{-1}
+    const int DP = D * P;
+    for (int d = 0; d < D; ++d)
+        for (int i0 = 0; i0 < P; i0 += 16)
+            for (int fc = 0; fc < 2; ++fc) {
+                if (!mine()) continue;
+                const int i = i0 + l16 < P ? i0 + l16 : P - 1;
+                d4 acc = {};
+                if (fc)
+                    mma16s<false, true>(LQf, seq(uhf, 1), seq(phif + i, P, ndA + d, D), acc);
+                else
+                    mma16s<false, true>(Qv, seq(uq, 1), seq(dphi + i * D + d, DP, wdet, 1), acc);
+                // all 16 rows are alike
+                if (lq == 0 && i0 + l16 < P) (fc ? q : t)[d * P + i0 + l16] = fc ? acc[0] : -acc[0];
+            }
     __syncthreads();
-    for (int k = tid; k < D * P; k += EBS) {
-        const int d = k / P, i = k - d * P;
-        double s = 0.0;
-        for (int j = 0; j < P; ++j) s += Mm[i * P + j] * t[d * P + j];
-        q[k] = -s;
-        if (a.q) a.q[k] = -s;
+    for (int k = tid; k < DP; k += BS) t[k] += q[k];
+    __syncthreads();
+    for (int i0 = 0; i0 < P; i0 += 16) {
+        if (!mine()) continue;
+        const int i = i0 + l16 < P ? i0 + l16 : P - 1, d = l16 < D ? l16 : 0;
+        d4 acc = {};
+        mma16s<false, false>(P, seq(t + d * P, 1), seq(Mm + i * P, 1), acc);
+        if (lq < D && i0 + l16 < P) {                    // D <= 3 < 4 rows: register 0
+            q[lq * P + i0 + l16] = acc[0];
+            if (a.q) a.q[lq * P + i0 + l16] = acc[0];
+        }
     }
     __syncthreads();
 
     // 5. q at the points, then the flux and its derivatives per point
-    for (int k = tid; k < Qv * D; k += EBS) {
-        const int x = k / D, d = k - x * D;
-        double s = 0.0;
-        for (int i = 0; i < P; ++i) s += phi[x * P + i] * q[d * P + i];
-        qq[k] = s;
-    }
-    for (int k = tid; k < L * Qf * D; k += EBS) {
-        const int lx = k / D, d = k - lx * D;
-        double s = 0.0;
-        for (int i = 0; i < P; ++i) s += phif[lx * P + i] * q[d * P + i];
-        qf[k] = s;
+    for (int vol = 1; vol >= 0; --vol) {
+        const int n = vol ? Qv : LQf;
+        for (int x0 = 0; x0 < n; x0 += 16) {
+            if (!mine()) continue;
+            const int x = x0 + l16 < n ? x0 + l16 : n - 1, d = l16 < D ? l16 : 0;
+            d4 acc = {};
+            mma16s<false, false>(P, seq((vol ? phi : phif) + x * P, 1), seq(q + d * P, 1), acc);
+            double* dst = vol ? qq : qf;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (x0 + 4 * r + lq < n && l16 < D) dst[(x0 + 4 * r + lq) * D + l16] = acc[r];
+        }
     }
     __syncthreads();
     const double nu = a.nu, tau = a.tau;
-    for (int k = tid; k < Qv * D; k += EBS) {
-        const int x = k / D, d = k - x * D;
-        const double v = uq[x];
-        const double bt = sel3(a.beta, d), gm = sel3(a.gamma, d);
-        wF[k] = wdet[x] * (bt * 0.5 * v * v + gm * v - nu * qq[k]);
-        wFu[k] = wdet[x] * (bt * v + gm);
+    for (int x = tid; x < Qv; x += BS) {
+        const double v = uq[x], w = wdet[x];
+        for (int d = 0; d < D; ++d) {
+            const double bt = sel3(a.beta, d), gm = sel3(a.gamma, d);
+            wF[x * D + d] = w * (bt * 0.5 * v * v + gm * v - nu * qq[x * D + d]);
+            wFu[x * D + d] = w * (bt * v + gm);
+        }
+        // the source and time term, over u_n at the points
+        duq[x] = w * (src[x] - (cdt != 0.0 ? cdt * (v - duq[x]) : 0.0));
     }
-    for (int lx = tid; lx < L * Qf; lx += EBS) {
+    for (int lx = tid; lx < LQf; lx += BS) {
         const double v = uhf[lx];
         double fn = 0.0, zn = 0.0;
         for (int d = 0; d < D; ++d) {
@@ -246,19 +277,23 @@ __device__ __forceinline__ void element_body(const ElemView& a, double* sm) {
     }
     __syncthreads();
 
-    // 6. right-hand sides ru = -R_u, rt = -R_t
-    for (int i = tid; i < P; i += EBS) {
-        double s = 0.0;
-        for (int x = 0; x < Qv; ++x) {
-            double g = 0.0;
-            for (int d = 0; d < D; ++d) g += wF[x * D + d] * dphi[(x * P + i) * D + d];
-            s += g + wdet[x] * (src[x] - cdt * duq[x]) * phi[x * P + i];
+    // 6. right-hand sides ru = -R_u, rt = -R_t. The D + 2 sums of ru (a dimension of (F, grad phi) each,
+    //    the source and time term, the faces) go to min(4, 2 D) partials over the room of t and q,
+    //    added in order.
+    const int np = 2 * D < 4 ? 2 * D : 4;
+    for (int slot = 0; slot < np; ++slot)
+        for (int i0 = 0; i0 < P; i0 += 16) {
+            if (!mine()) continue;
+            const int i = i0 + l16 < P ? i0 + l16 : P - 1;
+            d4 acc = {}, fc = {};
+            for (int sum = slot; sum < D + 2; sum += np) {
+                if (sum < D) mma16s<false, false>(Qv, seq(wF + sum, D), seq(dphi + i * D + sum, DP), acc);
+                else if (sum == D) mma16s<false, false>(Qv, seq(duq, 1), seq(phi + i, P), acc);
+                else mma16s<false, false>(LQf, seq(fhat, 1), seq(phif + i, P), fc);
+            }
+            if (lq == 0 && i0 + l16 < P) t[slot * P + i0 + l16] = acc[0] - fc[0];
         }
-        for (int lx = 0; lx < L * Qf; ++lx) s -= fhat[lx] * phif[lx * P + i];
-        if (a.r_extra) s -= a.r_extra[i];
-        a.ru[i] = s;
-    }
-    for (int k = tid; k < nt; k += EBS) {
+    for (int k = tid; k < nt; k += BS) {
         const int l = k / PF, j = k - l * PF;
         const bool bd = a.bnd[l] != 0;
         double s = 0.0;
@@ -268,97 +303,137 @@ __device__ __forceinline__ void element_body(const ElemView& a, double* sm) {
         }
         a.rt[k] = s;
     }
+    __syncthreads();
+    for (int i = tid; i < P; i += BS) {
+        double s = t[i];
+        for (int w = 1; w < np; ++w) s += t[w * P + i];
+        if (a.r_extra) s -= a.r_extra[i];
+        a.ru[i] = s;
+    }
     if (a.residual_only) return;
 
     // 7. matrices. With dF/dq = -nu I: the volume part of D is nu B_d, and G on an interior
-    // face is -nu C_d^T; the (i, j) sums over volume and face points share one pass with
-    // the row's per-point values held in registers.
+    // face is -nu C_d^T.
     const bool put_mass = !a.keep_mass;      // Minv, Bd, Cd: written unless kept
     if (put_mass)
-        for (int k = tid; k < P * P; k += EBS) a.Minv[k] = Mm[k];
-    for (int it = tid; it < P * nJT; it += EBS) {        // Bd, D, E
-        const int i = it / nJT, j0 = (it - i * nJT) * TJ;
-        double bd[3][TJ] = {}, sf[3][TJ] = {}, ev[TJ] = {}, ef[TJ] = {}, mm[TJ] = {};
-        for (int x = 0; x < Qv; ++x) {
-            const double wp = wdet[x] * phi[x * P + i];
-            double wd[3], g = 0.0;
+        for (int k = tid; k < P * P; k += BS) a.Minv[k] = Mm[k];
+    for (int i0 = 0; i0 < P; i0 += 16)                      // Bd, D, E
+        for (int j0 = 0; j0 < P; j0 += 16) {
+            if (!mine()) continue;
+            const int i = i0 + l16 < P ? i0 + l16 : P - 1, j = j0 + l16 < P ? j0 + l16 : P - 1;
+            d4 bd[D] = {}, ev = {};
+            auto vol = [&](const double* pw, const double* pj, const double* pi, const double* pd, const double* pf, bool in) {
+                const double w = in ? *pw : 0.0;
+                double g = cdt * w * *pi;
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const double dp = d < D ? dphi[(x * P + i) * D + d] : 0.0;
-                wd[d] = wdet[x] * dp;
-                g += d < D ? wFu[x * D + d] * dp : 0.0;
+                for (int d = 0; d < D; ++d) {
+                    g -= in ? pf[d] * pd[d] : 0.0;
+                    bd[d] = __builtin_amdgcn_mfma_f64_16x16x4f64(w * pd[d], *pj, bd[d], 0, 0, 0);
+                }
+                ev = __builtin_amdgcn_mfma_f64_16x16x4f64(g, *pj, ev, 0, 0, 0);
+            };
+            int left = Qv;
+            {
+                const int k = lq * P;
+                const double *pw = wdet + lq, *pj = phi + k + j, *pi = phi + k + i, *pd = dphi + (k + i) * D, *pf = wFu + lq * D;
+                for (; left >= 4; left -= 4, pw += 4, pj += 4 * P, pi += 4 * P, pd += 4 * DP, pf += 4 * D)
+                    vol(pw, pj, pi, pd, pf, true);
+                if (left > 0) {
+                    const bool in = lq < left;
+                    const int o = in ? 0 : left - 1 - lq;
+                    vol(pw + o, pj + o * P, pi + o * P, pd + o * DP, pf + o * D, in);
+                }
             }
+            if (put_mass)
 #pragma unroll
-            for (int jj = 0; jj < TJ; ++jj) {
-                const double pj = j0 + jj < P ? phi[x * P + j0 + jj] : 0.0;
+                for (int d = 0; d < D; ++d)
 #pragma unroll
-                for (int d = 0; d < 3; ++d) bd[d][jj] += wd[d] * pj;
-                ev[jj] -= g * pj;
-                mm[jj] += wp * pj;
+                    for (int r = 0; r < 4; ++r)
+                        if (i0 + 4 * r + lq < P && j0 + l16 < P)
+                            a.Bd[(size_t)(d * P + i0 + 4 * r + lq) * P + j0 + l16] = bd[d][r];
+            auto face = [&](const double* pa, const double* pi, const double* pj, const double* pn, bool in) {
+                const double v = in ? *pi : 0.0;
+#pragma unroll
+                for (int d = 0; d < D; ++d)
+                    bd[d] = __builtin_amdgcn_mfma_f64_16x16x4f64(-pn[d] * v, *pj, bd[d], 0, 0, 0);
+                ev = __builtin_amdgcn_mfma_f64_16x16x4f64(tau * *pa * v, *pj, ev, 0, 0, 0);
+            };
+            left = LQf;
+            {
+                const double *pa = dA + lq, *pi = phif + lq * P + i, *pj = phif + lq * P + j, *pn = ndA + lq * D;
+                for (; left >= 4; left -= 4, pa += 4, pi += 4 * P, pj += 4 * P, pn += 4 * D) face(pa, pi, pj, pn, true);
+                if (left > 0) {
+                    const bool in = lq < left;
+                    const int o = in ? 0 : left - 1 - lq;
+                    face(pa + o, pi + o * P, pj + o * P, pn + o * D, in);
+                }
+            }
+            const int jr = j0 + l16;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int ir = i0 + 4 * r + lq;
+                if (ir >= P || jr >= P) continue;
+#pragma unroll
+                for (int d = 0; d < D; ++d)
+                    a.D[ir * DP + d * P + jr] = nu * bd[d][r];
+                a.E[ir * P + jr] = ev[r];
             }
         }
-        for (int lx = 0; lx < L * Qf; ++lx) {
-            const double pi = phif[lx * P + i];
-            double nd[3];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) nd[d] = d < D ? ndA[lx * D + d] * pi : 0.0;
-            const double da = dA[lx] * pi;
-#pragma unroll
-            for (int jj = 0; jj < TJ; ++jj) {
-                const double pj = j0 + jj < P ? phif[lx * P + j0 + jj] : 0.0;
-#pragma unroll
-                for (int d = 0; d < 3; ++d) sf[d][jj] += nd[d] * pj;
-                ef[jj] += da * pj;
-            }
-        }
-#pragma unroll
-        for (int jj = 0; jj < TJ; ++jj) {
-            const int j = j0 + jj;
-            if (j >= P) continue;
-            for (int d = 0; d < D; ++d) {
-                if (put_mass) a.Bd[(size_t)(d * P + i) * P + j] = bd[d][jj];
-                a.D[(size_t)i * D * P + d * P + j] = nu * (bd[d][jj] - sf[d][jj]);
-            }
-            a.E[(size_t)i * P + j] = ev[jj] + tau * ef[jj] + cdt * mm[jj];
-        }
-    }
-    for (int it = tid; it < P * nt; it += EBS) {          // Cd, F, G, H for one (i, l, j)
-        const int i = it / nt, c = it - i * nt, l = c / PF, j = c - l * PF;
-        double cd[3] = {}, f = 0.0, h = 0.0;
-        for (int x = 0; x < Qf; ++x) {
-            const int lx = l * Qf + x;
-            const double w = phif[lx * P + i] * psi[x * PF + j];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) cd[d] -= d < D ? ndA[lx * D + d] * w : 0.0;
-            f += Z[lx] * w;
-            h += dA[lx] * w;
-        }
+    for (int l = 0; l < L; ++l) {
         const bool interior = a.bnd[l] == 0;
-        for (int d = 0; d < D; ++d) {
-            if (put_mass) a.Cd[(size_t)(d * P + i) * nt + c] = cd[d];
-            a.G[(size_t)c * D * P + d * P + i] = interior ? -nu * cd[d] : 0.0;
-        }
-        a.F[(size_t)i * nt + c] = f;
-        a.H[(size_t)c * P + i] = interior ? -tau * h : 0.0;
-    }
-    for (int k = tid; k < nt * nt; k += EBS) {              // J[(l,j)][(l',j')], block diagonal in l
-        const int r = k / nt, c = k - r * nt, l = r / PF, j = r - l * PF, l2 = c / PF, j2 = c - l2 * PF;
-        double s = 0.0;
-        if (l == l2) {
-            const bool bd = a.bnd[l] != 0;
-            for (int x = 0; x < Qf; ++x) {
-                const int lx = l * Qf + x;
-                s += (bd ? dA[lx] : -Z[lx]) * psi[x * PF + j] * psi[x * PF + j2];
+        for (int j0 = 0; j0 < PF; j0 += 16) {
+            const int j = j0 + l16 < PF ? j0 + l16 : PF - 1;
+            for (int i0 = 0; i0 < P; i0 += 16) {            // rows j, columns i: Cd, F, G, H
+                if (!mine()) continue;
+                const int i = i0 + l16 < P ? i0 + l16 : P - 1;
+                d4 cd[D] = {}, f = {}, h = {};
+                for (int x0 = 0; x0 < Qf; x0 += 4) {
+                    const int xk = x0 + lq, x = xk < Qf ? xk : Qf - 1, lx = l * Qf + x;
+                    const double ps = xk < Qf ? psi[x * PF + j] : 0.0, pi = phif[lx * P + i];
+#pragma unroll
+                    for (int d = 0; d < D; ++d)
+                        cd[d] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ndA[lx * D + d] * ps, pi, cd[d], 0, 0, 0);
+                    f = __builtin_amdgcn_mfma_f64_16x16x4f64(xk < Qf ? Z[lx] * ps : 0.0, pi, f, 0, 0, 0);
+                    h = __builtin_amdgcn_mfma_f64_16x16x4f64(dA[lx] * ps, pi, h, 0, 0, 0);
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int jr = j0 + 4 * r + lq, ir = i0 + l16, c = l * PF + jr;
+                    if (jr >= PF || ir >= P) continue;
+#pragma unroll
+                    for (int d = 0; d < D; ++d) {
+                            if (put_mass) a.Cd[(d * P + ir) * nt + c] = cd[d][r];
+                        a.G[c * DP + d * P + ir] = interior ? -nu * cd[d][r] : 0.0;
+                    }
+                    a.F[ir * nt + c] = f[r];
+                    a.H[c * P + ir] = interior ? -tau * h[r] : 0.0;
+                }
+            }
+            for (int k0 = 0; k0 < PF; k0 += 16) {           // J[(l,j)][(l,j')]
+                if (!mine()) continue;
+                const int k = k0 + l16 < PF ? k0 + l16 : PF - 1;
+                d4 acc = {};
+                mma16s<true, false>(Qf, seq(psi + j, PF, (interior ? Z : dA) + l * Qf, 1), seq(psi + k, PF), acc);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (j0 + 4 * r + lq < PF && k0 + l16 < PF)
+                        a.J[(l * PF + j0 + 4 * r + lq) * nt + l * PF + k0 + l16] = interior ? -acc[r] : acc[r];
             }
         }
-        a.J[k] = s;
+    }
+    // J is block diagonal in l
+    for (int row = wave, lo = 0; row < nt; row += NW) {
+        while (row >= lo + PF) lo += PF;
+        for (int c = lane; c < nt; c += 64)
+            if (c < lo || c >= lo + PF) a.J[row * nt + c] = 0.0;
     }
 }
 
-__global__ void __launch_bounds__(EBS) k_element_blocks(ElemArgs a) {
+template <int D>
+__global__ void __launch_bounds__(EBS, 4) k_element_blocks(ElemArgs a) {
     extern __shared__ double sm[];
     const size_t E = blockIdx.x;
-    const int P = a.P, PF = a.PF, L = a.L, D = a.D, Qv = a.g.nqv, Qf = a.g.nqf, nt = L * PF;
+    const int P = a.P, PF = a.PF, L = a.L, Qv = a.g.nqv, Qf = a.g.nqf, nt = L * PF;
     ElemView v;
     v.wdet = a.g.wdet + E * Qv;
     v.dphix = a.g.dphix + E * Qv * P * D;
@@ -395,12 +470,12 @@ __global__ void __launch_bounds__(EBS) k_element_blocks(ElemArgs a) {
     v.nu = a.m.nu; v.tau = a.m.tau; v.c = a.c;
     for (int d = 0; d < 3; ++d) { v.beta[d] = a.m.beta[d]; v.gamma[d] = a.m.gamma[d]; }
     v.bad = a.bad;
-    element_body(v, sm);
+    element_body<D>(v, sm);
 }
 
 // Batched instances: element e belongs to instance eid[e]; its arrays sit at the instance's
 // offsets plus its instance-local index times the per-element sizes.
-__global__ void __launch_bounds__(EBS) k_element_blocks_batch(const ElemInst* __restrict__ inst,
+__global__ void __launch_bounds__(128, 3) k_element_blocks_batch(const ElemInst* __restrict__ inst,
                                                               const int32_t* __restrict__ eid, ElemBatchArgs a) {
     extern __shared__ double sm[];
     const int64_t e = blockIdx.x;
@@ -443,7 +518,9 @@ __global__ void __launch_bounds__(EBS) k_element_blocks_batch(const ElemInst* __
     v.nu = q.nu; v.tau = q.tau; v.c = q.c;
     for (int d = 0; d < 3; ++d) { v.beta[d] = q.beta[d]; v.gamma[d] = q.gamma[d]; }
     v.bad = a.bad;
-    element_body(v, sm);
+    if (v.Dm == 2) element_body<2>(v, sm);
+    else if (v.Dm == 3) element_body<3>(v, sm);
+    else element_body<1>(v, sm);
 }
 
 // ||R|| of instance blockIdx.x: its element u-rows and its faces' summed trace rows.
@@ -500,7 +577,7 @@ size_t element_batch_lds_bytes(int P, int PF, int L, int D, int nqv, int nqf) {
 hdg_status element_blocks_batch_run(hdg_ctx ctx, int64_t total_ne, const ElemInst* inst_dev, const int32_t* eid,
                                     const ElemBatchArgs& a, size_t lds) {
     if (total_ne == 0) return HDG_OK;
-    hipLaunchKernelGGL(k_element_blocks_batch, dim3((unsigned)total_ne), dim3(EBS), lds, ctx->stream, inst_dev, eid, a);
+    hipLaunchKernelGGL(k_element_blocks_batch, dim3((unsigned)total_ne), dim3(128), lds, ctx->stream, inst_dev, eid, a);
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }
@@ -549,7 +626,11 @@ hdg_status element_blocks_run(hdg_ctx ctx, const hdg_dims* d, const hdg_elem_geo
     a.residual_only = (flags & HDG_ELEM_RESIDUAL_ONLY) != 0;
     a.keep_mass = (flags & HDG_ELEM_KEEP_MASS) != 0;
     const size_t lds = element_blocks_lds_bytes(d, g->nqv, g->nqf);
-    hipLaunchKernelGGL(k_element_blocks, dim3(d->ne), dim3(EBS), lds, ctx->stream, a);
+    const void* k = d->dim == 2   ? (const void*)k_element_blocks<2>
+                    : d->dim == 3 ? (const void*)k_element_blocks<3>
+                                  : (const void*)k_element_blocks<1>;
+    void* args[] = {(void*)&a};
+    HDG_HIP_CHECK(ctx, hipLaunchKernel(k, dim3(d->ne), dim3(elem_threads(d->npe)), args, lds, ctx->stream));
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }

@@ -1,6 +1,8 @@
 // Wave-level helpers shared by the recovery, condensation and block-Jacobi kernels (64-lane waves).
 #pragma once
 
+#include <cstdint>
+
 #include <hip/hip_runtime.h>
 
 namespace wave_ops {
@@ -66,6 +68,19 @@ __device__ __forceinline__ double wave_sum_all(double v) {
     return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
+// Copies `bytes` (a multiple of 4) from global memory to LDS without a round trip through registers;
+// wave `wave` of `nw` takes every nw-th piece of 256 bytes. Both sides need 4-byte alignment only.
+// Complete for the whole block after copies_done() and a barrier.
+__device__ __forceinline__ void copy_to_lds(const void* g, void* lds, int bytes, int wave, int nw) {
+    const int lane = threadIdx.x & 63;
+    for (int o = wave * 256; o < bytes; o += nw * 256)
+        if (o + lane * 4 < bytes)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) uint32_t*)((const char*)g + o + lane * 4),
+                (__attribute__((address_space(3))) uint32_t*)((char*)lds + o), 4, 0, 0);
+}
+__device__ __forceinline__ void copies_done() { __builtin_amdgcn_s_waitcnt(0x0F70); }    // vmcnt(0)
+
 // acc += A B for one 16 x 16 tile over K terms on the FP64 matrix cores (v_mfma_f64_16x16x4f64:
 // A[i][k] in lane i+16k, B[k][j] in lane j+16k; the result's entry (i, j) in lane
 // j+16(i mod 4), register i div 4). fa(k) gives this lane's A[lane mod 16][k], fb(k) its
@@ -92,6 +107,62 @@ __device__ __forceinline__ void mma16(int K, const FA& fa, const FB& fb, d4& acc
         a = k < K ? a : 0.0;
         b = k < K ? b : 0.0;
         acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+    }
+}
+
+// This lane's entries of an operand: entry k at p[k s], times w[k ws] where weighted.
+struct Seq {
+    const double* p;
+    int s;
+    const double* w;
+    int ws;
+};
+__device__ __forceinline__ Seq seq(const double* p, int s) { return {p, s, nullptr, 0}; }
+__device__ __forceinline__ Seq seq(const double* p, int s, const double* w, int ws) { return {p, s, w, ws}; }
+
+// mma16 over strided operands: running pointers instead of an index product per load, and all steps
+// of a remainder below 16 terms in flight together.
+template <bool WA, bool WB>
+__device__ __forceinline__ void mma16s(int K, const Seq& A, const Seq& B, d4& acc) {
+    const int kq = (threadIdx.x & 63) >> 4;
+    const double *pa = A.p + __mul24(kq, A.s), *pb = B.p + __mul24(kq, B.s);
+    const double *wa = WA ? A.w + __mul24(kq, A.ws) : nullptr, *wb = WB ? B.w + __mul24(kq, B.ws) : nullptr;
+    int left = K;
+    for (; left >= 16; left -= 16) {
+        double a[4], b[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            a[s] = *pa;
+            b[s] = *pb;
+            if (WA) a[s] *= *wa;
+            if (WB) b[s] *= *wb;
+            pa += 4 * A.s;
+            pb += 4 * B.s;
+            if (WA) wa += 4 * A.ws;
+            if (WB) wb += 4 * B.ws;
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
+    }
+    if (left > 0) {
+        double a[4], b[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (4 * s >= left) break;
+            const bool in = 4 * s + kq < left;
+            const int o = in ? 4 * s : left - 1 - kq;          // past the end: the last entry, then zeroed
+            a[s] = pa[__mul24(o, A.s)];
+            b[s] = pb[__mul24(o, B.s)];
+            if (WA) a[s] *= wa[__mul24(o, A.ws)];
+            if (WB) b[s] *= wb[__mul24(o, B.ws)];
+            a[s] = in ? a[s] : 0.0;
+            b[s] = in ? b[s] : 0.0;
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (4 * s >= left) break;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
+        }
     }
 }
 
