@@ -187,7 +187,27 @@ struct GmresCtl {
     double beta;        // cycle-start residual norm
     double est;         // latest Givens residual estimate
     double pad;
+    long long ticks[3]; // one-workgroup cycle: clock ticks of preconditioner, product, orthogonalisation
 };
+// One restart cycle of a small system in one workgroup (k_small.hip).
+constexpr int SMALL_CYCLE_MAX = 2048;
+struct SmallCycle {
+    int N, nf, nb, S, L;
+    const double* K64;      // the residual's operator
+    const void* K;          // the steps' operator (FP32 or FP64)
+    const void* Binv;       // block-Jacobi inverses of that precision, or null: z = v
+    const int32_t* nbr;
+    const double* b;
+    double* x;
+    double* V;
+    size_t ld;
+    double* H;
+    int ldh, jmax, passes;  // Gram-Schmidt passes a step
+    double target;
+    double* hist;
+    GmresCtl* ctl;
+};
+hdg_status small_cycle(hdg_ctx ctx, const SmallCycle& a, bool fp32);
 hdg_status krylov_cycle_init(hdg_ctx ctx, GmresCtl* ctl, const double* part, int nblk, double* g,
                              int jmax, double target);
 hdg_status krylov_scale_by(hdg_ctx ctx, double* v, const double* src, size_t n, const double* denom,

@@ -100,6 +100,15 @@ hdg_status op_B(hdg_ctx ctx, const Op& op, const double* x, const FaceEpilogue& 
     return face_op(ctx, op.nf, op.nb, op.S, op.L, op.K, op.k32, op.nbr, M2, op.b32, x, e, skip);
 }
 
+// Whether a cycle in one workgroup beats a step of ten launches (figures in k_small.hip): the vectors fit its
+// LDS, and a sweep over the operator's rows is at most 60,000 entries, what one CU reads from L2 in about the
+// time of the launches. Delayed CGS2 (four launches a step), modified Gram-Schmidt and other preconditioners
+// stay with the general path.
+bool small_cycle_fits(size_t N, int S, int nb, int orth, int prec) {
+    return (orth == HDG_ORTH_CGS2 || orth == HDG_ORTH_CGS) && (prec == HDG_PREC_NONE || prec == HDG_PREC_BJ) &&
+           N <= SMALL_CYCLE_MAX && N * (size_t)(nb * S) <= 60000;
+}
+
 struct PolyPlan {
     int kind = HDG_PREC_BJ;        // BJ_POLY or BJ_CHEB
     std::vector<double> tre, tim;  // Leja-ordered Ritz values
@@ -632,10 +641,25 @@ hdg_status solve_run(hdg_ctx ctx, const hdg_dims* d, const double* K64, const fl
         e.a[0] = 1.0;
         return op_bj(ctx, op64, u, e, nullptr);
     };
+    // a small system's cycle runs in one workgroup, which counts its phases' clock ticks itself
+    const bool small = small_cycle_fits(N, S, nb, o->orth, prec);
+    int clock_khz = 0;
+    if (small && timed)
+        HDG_HIP_CHECK(ctx, hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, ctx->device));
     // One restart cycle, entirely on the stream: FP64 residual, Arnoldi steps
     // (skipped on the device once converged), back substitution, x += Z y.
     auto enqueue_cycle = [&](int jmax) -> hdg_status {
         hdg_status s2;
+        if (small) {
+            SmallCycle a;
+            a.N = (int)N; a.nf = nf; a.nb = nb; a.S = S; a.L = L;
+            a.K64 = K64; a.K = opi.K; a.nbr = nbr; a.b = b; a.x = x;
+            a.Binv = opi.pk == PK_BJ && prec == HDG_PREC_BJ ? opi.Binv : nullptr;
+            a.V = w.V; a.ld = w.ld; a.H = w.H; a.ldh = w.ldh;
+            a.jmax = jmax; a.passes = o->orth == HDG_ORTH_CGS ? 1 : 2;
+            a.target = target; a.hist = w.hist; a.ctl = w.ctl;
+            return small_cycle(ctx, a, opi.k32);
+        }
         FaceEpilogue e = epi0();
         e.out[0] = w.V;
         e.s[0] = -1.0;
@@ -724,7 +748,13 @@ hdg_status solve_run(hdg_ctx ctx, const hdg_dims* d, const double* K64, const fl
         }
         hist_push(hc.beta);
         for (int i = 0; i < hc.k; ++i) hist_push(hbuf[i]);
-        if (timed) {
+        if (timed && small) {
+            const double per = clock_khz > 0 ? 1e-3 / clock_khz : 0.0;
+            stats->t_prec += per * (double)hc.ticks[0];
+            stats->t_matvec += per * (double)hc.ticks[1];
+            stats->t_orth += per * (double)hc.ticks[2];
+            stats->n_timed += hc.k;
+        } else if (timed) {
             // steps at or beyond hc.k returned at once on the device flag: not counted
             const int nsteps = (dcgs2 && hc.k > 0 && hc.k < jmax) ? hc.k + 1 : hc.k;
             for (int j = 0; j < nsteps && j < jmax; ++j) {
