@@ -162,6 +162,7 @@ hdg_status hdg_destroy(hdg_ctx ctx) {
     for (int s = 0; s < WS_NSLOTS; ++s)
         if (ctx->ws[s]) (void)hipFree(ctx->ws[s]);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
+    if (ctx->progress) (void)hipHostFree(ctx->progress);
     delete ctx;
     return HDG_OK;
 }

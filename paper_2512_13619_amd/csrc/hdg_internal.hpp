@@ -41,8 +41,15 @@ struct BjSetupKey {
     int nf = 0, nb = 0, S = 0;
 };
 
+// How far the device is in the current restart cycle, in pinned host memory that the kernels write:
+// Arnoldi steps completed, and whether the cycle is done.
+struct HostProgress {
+    int step, done;
+};
+
 struct hdg_ctx_s {
     int device = 0;
+    HostProgress* progress = nullptr;   // allocated by the first solve
     hipStream_t stream = nullptr;
     hipStream_t cap_stream = nullptr;   // private stream for graph capture (created on first use)
     std::string err;
@@ -187,6 +194,7 @@ struct GmresCtl {
     double beta;        // cycle-start residual norm
     double est;         // latest Givens residual estimate
     double pad;
+    HostProgress* progress;  // the host's view of the cycle, or null
     long long ticks[3]; // one-workgroup cycle: clock ticks of preconditioner, product, orthogonalisation
 };
 // One restart cycle of a small system in one workgroup (k_small.hip).
@@ -209,7 +217,7 @@ struct SmallCycle {
 };
 hdg_status small_cycle(hdg_ctx ctx, const SmallCycle& a, bool fp32);
 hdg_status krylov_cycle_init(hdg_ctx ctx, GmresCtl* ctl, const double* part, int nblk, double* g,
-                             int jmax, double target);
+                             int jmax, double target, HostProgress* progress);
 hdg_status krylov_scale_by(hdg_ctx ctx, double* v, const double* src, size_t n, const double* denom,
                            const int* skip);
 hdg_status krylov_givens(hdg_ctx ctx, GmresCtl* ctl, const double* part, int nblk, double* H, int ldh,

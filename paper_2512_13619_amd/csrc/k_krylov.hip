@@ -132,7 +132,15 @@ __global__ __launch_bounds__(BS) void k_scale_by(double* v, const double* src, s
 }
 
 // Sum of the norm partials of the cycle-start residual; initialises the cycle.
-__global__ void k_cycle_init(GmresCtl* ctl, const double* part, int nblk, double* g, int jmax, double target) {
+// Tells the host how far the cycle is (system-scope stores to its pinned words).
+__device__ __forceinline__ void tell_host(HostProgress* p, int step, int done) {
+    if (!p) return;
+    __hip_atomic_store(&p->step, step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (done) __hip_atomic_store(&p->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ void k_cycle_init(GmresCtl* ctl, const double* part, int nblk, double* g, int jmax, double target,
+                             HostProgress* progress) {
     const int lane = threadIdx.x;
     double s = 0.0;
     for (int b = lane; b < nblk; b += 64) s += part[b];
@@ -147,6 +155,8 @@ __global__ void k_cycle_init(GmresCtl* ctl, const double* part, int nblk, double
         ctl->nonfinite = !isfinite(beta);
         ctl->done = (beta <= target || !isfinite(beta) || jmax <= 0) ? 1 : 0;
         g[0] = beta;
+        ctl->progress = progress;
+        tell_host(progress, 0, ctl->done);
     }
 }
 
@@ -195,7 +205,9 @@ __global__ void k_givens(GmresCtl* ctl, const double* part, int nblk, double* H,
     ctl->k = j + 1;
     if (hist) hist[j] = est;
     if (!isfinite(est) || !isfinite(col[j])) ctl->nonfinite = 1;
-    if (est <= ctl->target || hn == 0.0 || j + 1 >= ctl->jmax || !isfinite(est)) ctl->done = 1;
+    const bool stop = est <= ctl->target || hn == 0.0 || j + 1 >= ctl->jmax || !isfinite(est);
+    if (stop) ctl->done = 1;
+    tell_host(ctl->progress, j + 1, stop);
 }
 
 // y = R^{-1} g over the k steps of this cycle (upper triangular R in H, column-major).
@@ -516,6 +528,7 @@ __global__ __launch_bounds__(COEF_BS) void k_dcgs2_coef(GmresCtl* ctl, const dou
         if (!(rho > 0.0) || !isfinite(rho)) stop = 1;   // breakdown: the space is invariant
         if (finish) stop = 1;
         if (stop) ctl->done = 1;
+        tell_host(ctl->progress, j + 1, stop);
         sh_rho = rho;
         sh_stop = stop;
     }
@@ -729,8 +742,8 @@ hdg_status vec_lincomb(hdg_ctx ctx, size_t n, double* out, double a, const doubl
 }
 
 hdg_status krylov_cycle_init(hdg_ctx ctx, GmresCtl* ctl, const double* part, int nblk, double* g, int jmax,
-                             double target) {
-    hipLaunchKernelGGL(k_cycle_init, dim3(1), dim3(64), 0, ctx->stream, ctl, part, nblk, g, jmax, target);
+                             double target, HostProgress* progress) {
+    hipLaunchKernelGGL(k_cycle_init, dim3(1), dim3(64), 0, ctx->stream, ctl, part, nblk, g, jmax, target, progress);
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }
