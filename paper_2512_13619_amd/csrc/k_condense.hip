@@ -982,14 +982,22 @@ __global__ __launch_bounds__(256, 2) void k_cond_getrs(CondDims cd, long long nb
     const int nkb = (nu + 31) / 32;
     const double* De = dinv + (size_t)e * nkb * 2048;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // the slab's rows in the interchanged order
+    // the slab's rows in the interchanged order, and the first of its 32-row blocks with an entry:
+    // L leaves the blocks above it zero (half the forward sweep for the columns of the identity)
+    __shared__ int first;
+    if (threadIdx.x == 0) first = nkb;
+    __syncthreads();
+    int mine = nkb;
     for (int idx = threadIdx.x; idx < nu * 32; idx += 256) {
         const int i = idx >> 5, j = idx & 31;
         const bool ok = j < ncs;
         const double v = Te[(size_t)pe[i] * C + c0 + (ok ? j : 0)];
         Y[i * SLAB_LD + j] = ok ? v : 0.0;
+        if (ok && v != 0.0 && i >> 5 < mine) mine = i >> 5;
     }
+    if (mine < nkb) atomicMin(&first, mine);
     __syncthreads();
+    const int kb0 = first;
     // Y_kb <- inv(diagonal block) Y_kb, by one wave (a 32 x 32 x 32 product)
     auto diag = [&](int kb, int which) {
         const int r0 = kb * 32;
@@ -1061,7 +1069,7 @@ __global__ __launch_bounds__(256, 2) void k_cond_getrs(CondDims cd, long long nb
                 }
     };
     // forward: L (unit lower), 32-row blocks from the top
-    for (int kb = 0; kb < nkb; ++kb) {
+    for (int kb = kb0; kb < nkb; ++kb) {
         if (wave == 0) diag(kb, 0);
         __syncthreads();
         for (int t = kb + 1 + wave; t < nkb; t += 4) update(t, kb);
@@ -1509,7 +1517,8 @@ hdg_status set_kernel_lds(hdg_ctx ctx, const CondDims& cd, int NB) {
 // cd.C, trace rows at `bot`): LU of Ebar (L and U left in the first nu columns of the top
 // rows) and X = Ebar^{-1}[Fbar | r_u] in their other columns, then the Schur product into
 // Kout [n][nt][nt] and rout [n][nt]. A zero pivot records e_off + element in status. ipiv
-// (optional, [n][nu]) receives the row interchanges; without it they go to the workspace.
+// (optional, [n][nu]) receives the row interchanges; without it they go to the workspace. bot null (only
+// where nu > 192, whose Schur product is a kernel of its own): X alone.
 hdg_status eliminate_and_schur(hdg_ctx ctx, const CondDims& cd, int NB, int64_t n, double* top, double* bot,
                                double* Kout, double* rout, int* status, int64_t e_off, int32_t* ipiv = nullptr) {
     hdg_status st;
@@ -1566,6 +1575,7 @@ hdg_status eliminate_and_schur(hdg_ctx ctx, const CondDims& cd, int NB, int64_t 
     hipLaunchKernelGGL(k_cond_getrs, dim3((unsigned)((nslab + 7) / 8 * 8)), dim3(BS), getrs_lds_bytes(cd), ctx->stream,
                        cd, nslab, nsl, sw, top, (const int32_t*)perm, (const double*)dinv);
     HDG_LAUNCH_CHECK(ctx);
+    if (!bot) return HDG_OK;        // X alone
     const int tm_n = div_up(cd.nt, GT);
     const long long ntile = (long long)n * tm_n * tm_n;
     const long long nblk = (ntile + 7) / 8 * 8;
@@ -1577,40 +1587,36 @@ hdg_status eliminate_and_schur(hdg_ctx ctx, const CondDims& cd, int NB, int64_t 
 
 // ---- additive Schwarz subdomain inverses (Section 4.6) -----------------------------------------
 // T = [[P, I, 0], [I, 0, 0]] with P the element's enriched Schur complement: eliminating the
-// first nt columns leaves -P^{-1} where the Schur complement would be.
+// first nt columns leaves X = P^{-1} in the top rows' other columns and -P^{-1} where the Schur
+// complement would be. Edges above 192, whose Schur product is a kernel of its own, take X and
+// never form the trace rows (288: their fill and product were 1.7 of 6.9 ms for 729 elements).
 //   P = Kbar^e, except that the diagonal block of each local face l is the assembled K_ff of
 //   its face f = e2f[e][l] (= Kbar^{e1}_{l1 l1} + Kbar^{e2}_{l2 l2}; one term on a boundary).
+// A wave fills a row.
 __global__ __launch_bounds__(BS) void k_asm_fill(int nb, int L, const double* __restrict__ Kbar,
                                                  const double* __restrict__ K64, int S, const int32_t* __restrict__ e2f,
                                                  double* __restrict__ top, double* __restrict__ bot) {
     const long long e = blockIdx.x;
-    const int nt = L * nb, C = 2 * nt + 1;
+    const int nt = L * nb, C = 2 * nt + 1, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const double* Ke = Kbar + (size_t)e * nt * nt;
-    double* Te = top + (size_t)e * nt * C;
-    double* Be = bot + (size_t)e * nt * C;
-    for (int idx = threadIdx.x; idx < nt * C; idx += BS) {
-        const int r = idx / C, c = idx - r * C;
-        double v = 0.0, w = 0.0;
-        if (c < nt) {
-            const int lr = r / nb, lc = c / nb;
-            if (lr == lc) {
-                const long long f = e2f[e * L + lr];
-                v = K64[((size_t)f * S) * nb * nb + (size_t)(c - lc * nb) * nb + (r - lr * nb)];
-            } else {
-                v = Ke[(size_t)r * nt + c];
-            }
-            w = (c == r) ? 1.0 : 0.0;
-        } else if (c < 2 * nt) {
-            v = (c - nt == r) ? 1.0 : 0.0;
+    for (int r = wave; r < nt; r += BS / 64) {
+        const int lr = r / nb, rr = r - lr * nb, lo = lr * nb;
+        const double* Kf = K64 + (size_t)e2f[e * L + lr] * S * nb * nb + rr;
+        double* Te = top + ((size_t)e * nt + r) * C;
+        for (int c = lane; c < nt; c += 64)
+            Te[c] = (c >= lo && c < lo + nb) ? Kf[(size_t)(c - lo) * nb] : Ke[(size_t)r * nt + c];
+        for (int c = lane; c < nt + 1; c += 64) Te[nt + c] = c == r ? 1.0 : 0.0;
+        if (bot) {
+            double* Be = bot + ((size_t)e * nt + r) * C;
+            for (int c = lane; c < C; c += 64) Be[c] = c == r ? 1.0 : 0.0;
         }
-        Te[idx] = v;
-        Be[idx] = w;
     }
 }
 
-// inv[e][l][l'][col][row] = P^{-1}(l nb + row, l' nb + col) = -Kout[e][l nb + row][l' nb + col]
-// (the block row of unit (e, l), blocks column-major, as the face operator streams them).
-__global__ __launch_bounds__(BS) void k_asm_store(int nb, int L, const double* __restrict__ Kout,
+// inv[e][l][l'][col][row] = P^{-1}(l nb + row, l' nb + col) = sign * src[e][l nb + row][l' nb + col], src
+// with rows of ld entries, nt rows an element (the block row of unit (e, l), blocks column-major, as
+// the face operator streams them).
+__global__ __launch_bounds__(BS) void k_asm_store(int nb, int L, const double* __restrict__ src, int ld, double sign,
                                                   double* __restrict__ inv64, float* __restrict__ inv32) {
     const long long e = blockIdx.x;
     const int nt = L * nb;
@@ -1622,7 +1628,7 @@ __global__ __launch_bounds__(BS) void k_asm_store(int nb, int L, const double* _
         const int col = rem % nb; rem /= nb;
         const int lp = rem % L; rem /= L;
         const int l = rem;
-        const double v = -Kout[base + (size_t)(l * nb + row) * nt + (lp * nb + col)];
+        const double v = sign * src[((size_t)e * nt + l * nb + row) * ld + (lp * nb + col)];
         if (inv64) inv64[base + idx] = v;
         if (inv32) inv32[base + idx] = (float)v;
     }
@@ -1720,17 +1726,19 @@ hdg_status asm_setup_run(hdg_ctx ctx, const hdg_dims* d, const double* Kbar, con
         ctx->err = "additive Schwarz: element trace block too large for the LDS-blocked elimination";
         return HDG_ERR_SHAPE;
     }
-    const size_t per_elem = sizeof(double) * ((size_t)2 * cd.nt * cd.C + (size_t)cd.nt * cd.nt + cd.nt);
+    const bool x_alone = cd.nu > 192;
+    const size_t per_elem = sizeof(double) * (x_alone ? (size_t)cd.nt * cd.C
+                                                      : (size_t)2 * cd.nt * cd.C + (size_t)cd.nt * cd.nt + cd.nt);
     int64_t chunk = (int64_t)((size_t)4 << 30) / (int64_t)(per_elem + lu_ws_bytes_per_elem(cd));
     if (chunk < 1) chunk = 1;
     if (chunk > ne) chunk = ne;
     hdg_status st;
-    // workspace: top rows, trace rows, -P^{-1} and the (zero) right-hand-side output
+    // workspace: top rows and, unless X alone, trace rows, -P^{-1} and the (zero) right-hand-side output
     double* top = (double*)ws_get(ctx, WS_T_BOTTOM, per_elem * (size_t)chunk, &st);
     if (!top) return st;
-    double* bot = top + (size_t)chunk * cd.nt * cd.C;
-    double* Kout = bot + (size_t)chunk * cd.nt * cd.C;
-    double* rout = Kout + (size_t)chunk * cd.nt * cd.nt;
+    double* bot = x_alone ? nullptr : top + (size_t)chunk * cd.nt * cd.C;
+    double* Kout = x_alone ? nullptr : bot + (size_t)chunk * cd.nt * cd.C;
+    double* rout = x_alone ? nullptr : Kout + (size_t)chunk * cd.nt * cd.nt;
     int* status = (int*)ws_get(ctx, WS_STATUS, 64, &st);
     if (!status) return st;
     const int big = 0x7fffffff;
@@ -1743,7 +1751,9 @@ hdg_status asm_setup_run(hdg_ctx ctx, const hdg_dims* d, const double* Kbar, con
                            e2f + e0 * L, top, bot);
         HDG_LAUNCH_CHECK(ctx);
         if ((st = eliminate_and_schur(ctx, cd, NB, n, top, bot, Kout, rout, status, e0)) != HDG_OK) return st;
-        hipLaunchKernelGGL(k_asm_store, dim3((unsigned)n), dim3(BS), 0, ctx->stream, nb, L, Kout,
+        hipLaunchKernelGGL(k_asm_store, dim3((unsigned)n), dim3(BS), 0, ctx->stream, nb, L,
+                           x_alone ? (const double*)top + cd.nt : (const double*)Kout, x_alone ? cd.C : cd.nt,
+                           x_alone ? 1.0 : -1.0,
                            inv64 ? inv64 + e0 * nt2 : nullptr, inv32 ? inv32 + e0 * nt2 : nullptr);
         HDG_LAUNCH_CHECK(ctx);
     }
