@@ -415,10 +415,11 @@ __global__ __launch_bounds__(COEF_BS) void k_dcgs2_coef(GmresCtl* ctl, const dou
     __shared__ double tsh[201];
     __shared__ double hcol[202];        // column j-1 of Hu (rows 0..j)
     __shared__ double css[201], sns[201];
-    __shared__ double sh_rho;
-    __shared__ int sh_stop;
+    __shared__ double sh_rho, sh_ac;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int J = j + 1;
+    // what the serial part needs besides, on its way with the partials
+    const double g_old = j > 0 ? g[j - 1] : 0.0, target = ctl->target;
     // the block partials of the inner-product sweep, one wave per sum (each lane adds its
     // blocks in increasing order), three sums per pass so that each lane has 36 loads in
     // flight, and everything the serial part needs
@@ -489,20 +490,40 @@ __global__ __launch_bounds__(COEF_BS) void k_dcgs2_coef(GmresCtl* ctl, const dou
                 Hu[(size_t)(j - 1) * ldh + j] = rho;
             }
         }
+        if (lane == 0) {
+            sh_rho = rho;
+            sh_ac = ac;
+        }
     }
     __syncthreads();
+    rho = sh_rho;
+    // wave 0 closes column j-1 while wave 1 forms the new column: neither needs the other's result (after
+    // the last step of a cycle the new column is not read). One wave doing both in turn cost 0.6 us more
+    // of the launch's 11 at 34,000 unknowns (a Burgers DIRK step: 18.7 and 18.3 ms).
     if (tid == 0) {
         int stop = 0;
         if (j > 0) {
-            // Givens: previous rotations, a new one, the residual estimate (column j-1)
+            // Givens: previous rotations, a new one, the residual estimate (column j-1); eight
+            // rotations' operands ahead of the chain of dependent updates
             const int c0 = j - 1;
             double* col = H + (size_t)c0 * ldh;
             double hprev = hcol[0];
-            for (int i = 0; i < c0; ++i) {
-                const double hn = hcol[i + 1];
-                const double t = css[i] * hprev + sns[i] * hn;
-                col[i] = t;
-                hprev = -sns[i] * hprev + css[i] * hn;
+            for (int i = 0; i < c0; i += 8) {
+                double hn[8], cc[8], sv[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int q = i + u < c0 ? i + u : i;
+                    hn[u] = hcol[q + 1];
+                    cc[u] = css[q];
+                    sv[u] = sns[q];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (i + u >= c0) break;
+                    const double t = cc[u] * hprev + sv[u] * hn[u];
+                    col[i + u] = t;
+                    hprev = -sv[u] * hprev + cc[u] * hn[u];
+                }
             }
             const double hjj = hprev, hn = hcol[c0 + 1];
             double c = 1.0, sg = 0.0;
@@ -511,31 +532,27 @@ __global__ __launch_bounds__(COEF_BS) void k_dcgs2_coef(GmresCtl* ctl, const dou
                 c = hjj / r;
                 sg = hn / r;
             }
+            const double diag = c * hjj + sg * hn, gn = -sg * g_old, est = fabs(gn);
             cs[c0] = c;
             sn[c0] = sg;
-            col[c0] = c * hjj + sg * hn;
+            col[c0] = diag;
             col[c0 + 1] = 0.0;
-            const double gj = g[c0];
-            g[c0 + 1] = -sg * gj;
-            g[c0] = c * gj;
-            const double est = fabs(g[c0 + 1]);
+            g[c0 + 1] = gn;
+            g[c0] = c * g_old;
             ctl->est = est;
             ctl->k = j;
             if (hist) hist[c0] = est;
-            if (!isfinite(est) || !isfinite(col[c0])) ctl->nonfinite = 1;
-            if (est <= ctl->target || !isfinite(est)) stop = 1;
+            if (!isfinite(est) || !isfinite(diag)) ctl->nonfinite = 1;
+            if (est <= target || !isfinite(est)) stop = 1;
         }
         if (!(rho > 0.0) || !isfinite(rho)) stop = 1;   // breakdown: the space is invariant
         if (finish) stop = 1;
         if (stop) ctl->done = 1;
         tell_host(ctl->progress, j + 1, stop);
-        sh_rho = rho;
-        sh_stop = stop;
     }
-    __syncthreads();
-    if (sh_stop) return;
-    if (wave != 0) return;     // the rest is one wave's work (no barriers below)
-    const double irho = 1.0 / sh_rho;
+    if (wave != 1 || finish) return;
+    ac = sh_ac;
+    const double irho = 1.0 / rho;
     // t = Hu[:j+1, :j] a over the Hessenberg pattern (row i has entries in columns q >= i-1
     // only; nothing below the subdiagonal is ever read): column j-1 from LDS, the others
     // read eight at a time
