@@ -161,8 +161,9 @@ hdg_status hdg_assemble_rhs(hdg_ctx ctx, const hdg_dims* dims, const int32_t* f2
  * Right-preconditioned flexible GMRES(restart): every cycle starts from the true
  * FP64 residual r - K64 x; it stops when ||r - K64 x||_2 <= max(rtol*||r||_2, atol)
  * or after max_iters Arnoldi steps. The Hessenberg/Givens update runs on the
- * device in FP64; a whole cycle is enqueued at once (or replayed as one captured
- * hipGraph when use_graph = 1) and the host reads one status word per cycle.
+ * device in FP64; a cycle is enqueued a few steps ahead of the device until it has converged
+ * (or replayed as one captured hipGraph when use_graph = 1; a small system's runs in one
+ * kernel) and the host reads one status word per cycle.
  * With use_graph = 1 the solve drains the context's stream, runs on a private
  * stream of the context (so the caller's stream may be the legacy null stream)
  * and drains that stream before returning.
@@ -216,7 +217,8 @@ typedef struct {
                                    directly even when use_graph = 1). Where a phase starts or
                                    ends with a face-operator or delayed-CGS2 sweep kernel, the
                                    launch itself records the event at the kernel's start or end
-                                   (hipExtLaunchKernelGGL); elsewhere a plain event record. */
+                                   (hipExtLaunchKernelGGL); elsewhere a plain event record. A
+                                   small system's one-kernel cycle reads the device clock. */
     int32_t fold_prec;          /* 1 (with HDG_ORTH_DCGS2 and a preconditioner): form the
                                    right-preconditioned blocks K[f][s] P_g^{-1} (g = nbr(f,s))
                                    once per solve in a workspace, FP32 on the mixed path, so a

@@ -7,8 +7,9 @@
 // of iterative refinement. Orthogonalisation (CGS2 / CGS / MGS), the Hessenberg
 // Givens update and the solution update are FP64.
 //
-// Host/device traffic: the host enqueues a whole cycle (FP64 residual, all m
-// Arnoldi steps, back substitution, update), optionally as one captured hipGraph;
+// Host/device traffic: the host enqueues a cycle (FP64 residual, Arnoldi steps until it
+// sees that the cycle is done, back substitution, update), optionally whole as one captured
+// hipGraph; small systems run it in one kernel (k_small.hip);
 // every in-cycle kernel reads a device "done" word and returns at once after
 // convergence, so the host synchronises once per cycle.
 //
