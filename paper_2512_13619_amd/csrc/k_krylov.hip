@@ -131,7 +131,6 @@ __global__ __launch_bounds__(BS) void k_scale_by(double* v, const double* src, s
     v[k] = src[k] / *denom;
 }
 
-// Sum of the norm partials of the cycle-start residual; initialises the cycle.
 // Tells the host how far the cycle is (system-scope stores to its pinned words).
 __device__ __forceinline__ void tell_host(HostProgress* p, int step, int done) {
     if (!p) return;
@@ -139,6 +138,7 @@ __device__ __forceinline__ void tell_host(HostProgress* p, int step, int done) {
     if (done) __hip_atomic_store(&p->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Sum of the norm partials of the cycle-start residual; initialises the cycle.
 __global__ void k_cycle_init(GmresCtl* ctl, const double* part, int nblk, double* g, int jmax, double target,
                              HostProgress* progress) {
     const int lane = threadIdx.x;
@@ -174,6 +174,7 @@ __global__ void k_givens(GmresCtl* ctl, const double* part, int nblk, double* H,
                          double* sn, double* g, int j, double* hist) {
     if (ctl->done) return;
     const int lane = threadIdx.x;
+    HostProgress* const progress = ctl->progress;     // not behind the chain below
     double s = 0.0;
     for (int b = lane; b < nblk; b += 64) s += part[b];
     s = wave_sum(s);
@@ -207,7 +208,7 @@ __global__ void k_givens(GmresCtl* ctl, const double* part, int nblk, double* H,
     if (!isfinite(est) || !isfinite(col[j])) ctl->nonfinite = 1;
     const bool stop = est <= ctl->target || hn == 0.0 || j + 1 >= ctl->jmax || !isfinite(est);
     if (stop) ctl->done = 1;
-    tell_host(ctl->progress, j + 1, stop);
+    tell_host(progress, j + 1, stop);
 }
 
 // y = R^{-1} g over the k steps of this cycle (upper triangular R in H, column-major).
@@ -420,6 +421,7 @@ __global__ __launch_bounds__(COEF_BS) void k_dcgs2_coef(GmresCtl* ctl, const dou
     const int J = j + 1;
     // what the serial part needs besides, on its way with the partials
     const double g_old = j > 0 ? g[j - 1] : 0.0, target = ctl->target;
+    HostProgress* const progress = ctl->progress;
     // the block partials of the inner-product sweep, one wave per sum (each lane adds its
     // blocks in increasing order), three sums per pass so that each lane has 36 loads in
     // flight, and everything the serial part needs
@@ -548,7 +550,7 @@ __global__ __launch_bounds__(COEF_BS) void k_dcgs2_coef(GmresCtl* ctl, const dou
         if (!(rho > 0.0) || !isfinite(rho)) stop = 1;   // breakdown: the space is invariant
         if (finish) stop = 1;
         if (stop) ctl->done = 1;
-        tell_host(ctl->progress, j + 1, stop);
+        tell_host(progress, j + 1, stop);
     }
     if (wave != 1 || finish) return;
     ac = sh_ac;

@@ -586,7 +586,10 @@ hdg_status solve_run(hdg_ctx ctx, const hdg_dims* d, const double* K64, const fl
     // Enqueueing a whole cycle at once costs its idle launches where it converges early: a launch that
     // only finds the device flag still starts every block (8.6 us for 34,000 faces, eleven a polynomial
     // step). The host stays AHEAD steps before the device, which writes its progress to pinned memory,
-    // and stops once the cycle is done. Not under capture (a replayed cycle is fixed).
+    // and stops once the cycle is done. Not under capture (a replayed cycle is fixed). Fewer idle steps
+    // cost less (polynomial solve on 16,464 Navier-Stokes tets: 68.1 ms one step ahead, 69.6 six, 71.0
+    // twelve, 75.3 for whole cycles; others within 1%), but the host then has less time for a step's four
+    // to forty launches: six of the shortest steps are 150 us.
     constexpr int AHEAD = 6;
     if (!ctx->progress &&
         hipHostMalloc((void**)&ctx->progress, sizeof(HostProgress), hipHostMallocMapped | hipHostMallocCoherent) !=
@@ -604,8 +607,23 @@ hdg_status solve_run(hdg_ctx ctx, const hdg_dims* d, const double* K64, const fl
     auto cycle_done = [&](int j) -> bool {
         if (!dev_progress || capturing) return false;
         volatile HostProgress* p = ctx->progress;
-        for (int spin = 1; !p->done && p->step + AHEAD < j; ++spin)
-            if (spin % 4096 == 0 && hipStreamQuery(ctx->stream) != hipErrorNotReady) break;    // drained, or failed
+        // The stream itself is asked only after QUIET seconds without a step: a query puts a marker into
+        // it (asked every 4096 reads, 2 to 5 us a step: Burgers DIRK step, 5734 triangles, 18.2 and 17.2 ms).
+        constexpr double QUIET = 0.02;
+        int seen = -1;
+        double since = 0.0;
+        for (unsigned spin = 0; !p->done && p->step + AHEAD < j; ++spin) {
+            if (spin % 1024) continue;
+            const double t = now_s();
+            const int at = p->step;
+            if (at != seen) {
+                seen = at;
+                since = t;
+            } else if (t - since > QUIET) {
+                if (hipStreamQuery(ctx->stream) != hipErrorNotReady) break;    // drained, or failed
+                since = t;
+            }
+        }
         return p->done != 0;
     };
     // Delayed-CGS2 steps of one cycle (right preconditioning with a fixed preconditioner,
@@ -693,7 +711,8 @@ hdg_status solve_run(hdg_ctx ctx, const hdg_dims* d, const double* K64, const fl
         e.a[0] = 1.0;
         if ((s2 = face_op(ctx, nf, nb, S, L, K64, false, nbr, nullptr, false, x, e, nullptr)) != HDG_OK) return s2;
         if ((s2 = vec_sumsq_partial(ctx, w.V, N, w.part, w.nblk, nullptr)) != HDG_OK) return s2;
-        if ((s2 = krylov_cycle_init(ctx, w.ctl, w.part, w.nblk, w.g, jmax, target, dev_progress)) != HDG_OK)
+        if ((s2 = krylov_cycle_init(ctx, w.ctl, w.part, w.nblk, w.g, jmax, target,
+                                    capturing ? nullptr : dev_progress)) != HDG_OK)
             return s2;
         if ((s2 = krylov_scale_by(ctx, w.V, w.V, N, &w.ctl->beta, skip)) != HDG_OK) return s2;
         if (dcgs2) return enqueue_dcgs2_steps(jmax);
