@@ -198,7 +198,7 @@ struct GmresCtl {
     long long ticks[3]; // one-workgroup cycle: clock ticks of preconditioner, product, orthogonalisation
 };
 // One restart cycle of a small system in one workgroup (k_small.hip).
-constexpr int SMALL_CYCLE_MAX = 2048;
+constexpr int SMALL_CYCLE_MAX = 1920;
 struct SmallCycle {
     int N, nf, nb, S, L;
     const double* K64;      // the residual's operator

@@ -6,10 +6,19 @@
 // is a chain of barriers in one block: 16 waves take the operator rows, the inner products by columns
 // (four per wave at a time) and the updates by rows, the new vector and the rotations stay in LDS,
 // and only the basis and the operator come from L2. Where it stops to pay is where one CU's share of
-// the L2 bandwidth (the basis is read four times a step) costs more than the launches. Whole Newton
-// solves of a Poisson problem (GMRES(50), CGS2), general path and here: 5.4 and 1.6 ms with 432
-// unknowns, 7.9 and 4.5 ms with 1092, 10.0 and 9.2 ms with 1920 in blocks of 4 (54,000 entries of K a
-// row sweep): the limits of small_cycle_fits.
+// the L2 bandwidth (the basis is read four times a CGS2 step, twice a CGS step) costs more than the
+// launches. Time of a step (us) here and in the general path, in cycles that run their whole length (FP64,
+// block-Jacobi, blocks of 4 on quads, 28 entries of K a row; blocks of 1 are further ahead):
+//              CGS2, 10 columns   50          100         200         CGS, 50     100         200
+//   N =  256       16.2/33.3   16.0/39.6   19.2/56.9   27.2/91.4   12.2/34.2   14.0/42.8   18.9/61.4
+//   N = 1024       24.1/40.6   29.5/42.6   40.9/59.3   66.3/92.3   20.6/35.1   26.5/43.8   39.9/62.3
+//   N = 1408       31.6/41.4   40.3/43.3   56.9/60.5   93.7/94.7   27.9/36.1   36.4/44.6   55.7/63.5
+//   N = 1664       35.1/42.1   45.0/43.4   64.0/60.9  105.6/94.9   31.0/36.2   40.7/44.8   62.5/63.6
+//   N = 1792       36.1/43.5   46.3/44.8   65.4/61.5  107.8/95.0   31.9/36.3   41.6/45.1   63.8/63.9
+//   N = 1920       39.0/42.2   50.7/43.7   72.1/61.4  119.4/94.8   34.8/36.2   45.6/44.8   70.3/63.9
+// and whole Newton solves of a Poisson problem (GMRES(50), CGS2): 1.6 ms here and 5.4 with 432 unknowns,
+// 6.1 and 6.9 with 1440, 6.5 and 6.5 with 1680, 9.2 and 8.4 with 1920. Hence the limits of
+// small_cycle_fits. (1024 threads leave a thread 128 registers; 18 are spilled.)
 #include <cmath>
 
 #include "hdg_internal.hpp"

@@ -101,13 +101,18 @@ hdg_status op_B(hdg_ctx ctx, const Op& op, const double* x, const FaceEpilogue& 
     return face_op(ctx, op.nf, op.nb, op.S, op.L, op.K, op.k32, op.nbr, M2, op.b32, x, e, skip);
 }
 
-// Whether a cycle in one workgroup beats a step of ten launches (figures in k_small.hip): the vectors fit its
-// LDS, and a sweep over the operator's rows is at most 60,000 entries, what one CU reads from L2 in about the
-// time of the launches. Delayed CGS2 (four launches a step), modified Gram-Schmidt and other preconditioners
-// stay with the general path.
-bool small_cycle_fits(size_t N, int S, int nb, int orth, int prec) {
-    return (orth == HDG_ORTH_CGS2 || orth == HDG_ORTH_CGS) && (prec == HDG_PREC_NONE || prec == HDG_PREC_BJ) &&
-           N <= SMALL_CYCLE_MAX && N * (size_t)(nb * S) <= 60000;
+// Whether a cycle in one workgroup is no slower than the general path's ten launches a step (table in
+// k_small.hip): the vectors fit its LDS, a sweep over the operator's rows is at most 60,000 entries, what one
+// CU reads from L2 in about the time of the launches, and the basis, which a CGS2 step reads four times and a
+// CGS step twice, costs that CU no more than the launches either: a cycle that runs its whole length breaks
+// even near 1500 unknowns with CGS2 and 1900 with CGS, whatever the length from 50 columns on, since the
+// general path's sweeps grow with the columns too; a short cycle is ahead up to the LDS limit. Delayed CGS2
+// (four launches a step), modified Gram-Schmidt and other preconditioners stay with the general path.
+bool small_cycle_fits(size_t N, int S, int nb, int orth, int prec, int restart) {
+    if ((prec != HDG_PREC_NONE && prec != HDG_PREC_BJ) || N > SMALL_CYCLE_MAX || N * (size_t)(nb * S) > 60000)
+        return false;
+    if (orth == HDG_ORTH_CGS2) return N <= (restart <= 10 ? 1792 : 1408);
+    return orth == HDG_ORTH_CGS && N <= (restart <= 50 ? 1920 : 1664);
 }
 
 struct PolyPlan {
@@ -686,7 +691,7 @@ hdg_status solve_run(hdg_ctx ctx, const hdg_dims* d, const double* K64, const fl
         return op_bj(ctx, op64, u, e, nullptr);
     };
     // a small system's cycle runs in one workgroup, which counts its phases' clock ticks itself
-    const bool small = small_cycle_fits(N, S, nb, o->orth, prec);
+    const bool small = small_cycle_fits(N, S, nb, o->orth, prec, m);
     int clock_khz = 0;
     if (small && timed)
         HDG_HIP_CHECK(ctx, hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, ctx->device));
