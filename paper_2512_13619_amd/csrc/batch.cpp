@@ -125,6 +125,7 @@ hdg_status hdg_batch_create(hdg_ctx ctx, int32_t n_inst, const hdg_dims* dims_h,
             blk_hi.push_back(q.vec_off + std::min<int64_t>(n, k + SEG_CHUNK));
         }
         ib1[i] = (int32_t)blk_inst.size();
+        b->dev.max_chunks = std::max(b->dev.max_chunks, ib1[i] - ib0[i]);
         b->dev.max_nb = std::max(b->dev.max_nb, q.nb);
         b->dev.max_R = std::max(b->dev.max_R, q.R);
     }
@@ -438,7 +439,7 @@ hdg_status hdg_gmres_solve_batch(hdg_ctx ctx, hdg_batch b, const double* K64, co
     double* part = (double*)ws_get(ctx, WS_PART, sizeof(double) * (size_t)dv.nblk * (m + 1) * 2, &st);
     if (!part) return st;
     double* part2 = part + (size_t)dv.nblk * (m + 1);     // a sweep reads the partials of the one before
-    const size_t nctl = (size_t)ni * ((size_t)ldh * m + 5 * (size_t)ldg + 2);
+    const size_t nctl = (size_t)ni * ((size_t)ldh * m + 6 * (size_t)ldg + 2);
     char* base = (char*)ws_get(ctx, WS_CTL, sizeof(BatchCtl) * ni + sizeof(double) * nctl, &st);
     if (!base) return st;
     BatchCtl* ctl = (BatchCtl*)base;
@@ -448,7 +449,8 @@ hdg_status hdg_gmres_solve_batch(hdg_ctx ctx, hdg_batch b, const double* K64, co
     double* g = sn + (size_t)ni * ldg;
     double* y = g + (size_t)ni * ldg;
     double* bn = y + (size_t)ni * ldg;       // ||b||^2 per instance
-    double* target = bn + (size_t)ni * ldg;   // per-instance absolute target
+    double* coef = bn + (size_t)ni * ldg;
+    double* target = coef + (size_t)ni * ldg;   // per-instance absolute target
     const void* Kop = mixed ? (const void*)K32 : (const void*)K64;
     const void* Bop = nullptr;
     double* B64 = nullptr;
@@ -523,6 +525,7 @@ hdg_status hdg_gmres_solve_batch(hdg_ctx ctx, hdg_batch b, const double* K64, co
             SegSweep sw{};
             sw.V = V; sw.ldv = ld; sw.J = j + 1; sw.w = wv; sw.part_out = part;
             sw.col = col; sw.ld_col = ldh * m; sw.ctl = ctl;
+            sw.coef = coef; sw.ld_coef = ldg;
             if ((s2 = seg_sweep(ctx, dv, sw, false, true)) != HDG_OK) return s2;
             if (o->orth == HDG_ORTH_CGS2) {
                 sw.part_in = part; sw.part_out = part2;

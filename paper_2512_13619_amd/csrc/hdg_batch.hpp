@@ -42,15 +42,25 @@ inline int batch_team(int nb, int S) {
 // Entries of a reduction chunk. 96 instances of 270,000 unknowns in all give 580 blocks.
 constexpr int SEG_CHUNK = 512;
 
+// Chunks times columns above which an instance's partial inner products are added up once for all its
+// blocks, by a kernel of its own, instead of by every block: the blocks' reads grow with the square of
+// the instance's size. One instance, time of a step with both CGS2 passes: 100,000 unknowns (196
+// chunks), 30 columns 49.5 us by every block, 52.2 once; 100 columns 79.2 and 76.3; 272,000, 30
+// columns 84.0 and 83.6; 10^6, 30 columns 271 and 225; 8 10^6 5490 and 1690.
+constexpr int SEG_DIRECT = 8192;
+
 // One Gram-Schmidt sweep (k_seg_sweep): w against the J basis vectors V. part_in: the sweep's
-// coefficients as the partials of the sweep before; col: this step's Hessenberg column (stride
-// ld_col per instance), set or added to. The index arrays are the launcher's to fill in.
+// coefficients as the partials of the sweep before (coef: their sums, ld_coef per instance, for instances
+// above SEG_DIRECT); col: this step's Hessenberg column (stride ld_col per instance), set or added to. The
+// index arrays are the launcher's to fill in.
 struct SegSweep {
     const double* V;
     size_t ldv;
     int J;
     double* w;
     const double* part_in;
+    double* coef;
+    int ld_coef;
     double* part_out;
     double* col;
     int ld_col, add;
@@ -71,7 +81,7 @@ struct BatchDev {
     int64_t* blk_hi = nullptr;
     int32_t* ib0 = nullptr;         // [n_inst] first / one-past-last chunk of each instance
     int32_t* ib1 = nullptr;
-    int n_inst = 0, nblk = 0, nfblk = 0;
+    int n_inst = 0, nblk = 0, nfblk = 0, max_chunks = 0;
     int64_t total_ne = 0, total_nf = 0, total_dof = 0;
     size_t max_cond_lds = 0, max_rec_lds = 0;
     int max_nb = 0, max_snb = 0, max_R = 0;

@@ -358,8 +358,9 @@ __global__ __launch_bounds__(BS) void k_batch_bj(const InstDesc* __restrict__ de
 // Block b covers entries [blk_lo[b], blk_hi[b]) of instance blk_inst[b] (at most SEG_CHUNK; chunks
 // never straddle two instances). part[i * nblk + b].
 // One Gram-Schmidt sweep over an instance's basis: the coefficients h_i = sum_b part_in[i][b] of the
-// sweep before (AXPY; every block of the instance adds them up in the same order, its first block
-// puts them into the Hessenberg column), w -= V h, then the partial inner products V^T w (DOT) or
+// sweep before (AXPY; every block of the instance adds them up in the same order, or k_seg_coef has
+// done it in that order for all, see SEG_DIRECT; its first block puts them into the Hessenberg
+// column), w -= V h, then the partial inner products V^T w (DOT) or
 // ||w||^2. A wave takes four columns at a time with all their loads in flight; a sweep by one column
 // after another, with reductions in kernels of their own, took 31 + 4 + 7 us a sweep for 96
 // instances (270,000 unknowns, up to 30 columns, averages over cycles in which ever fewer are
@@ -377,15 +378,19 @@ __global__ __launch_bounds__(BS) void k_seg_sweep(SegSweep a) {
     double* w = a.w + k0;
     if constexpr (AXPY) {
         const int b0 = a.ib0[inst], b1 = a.ib1[inst];
-        for (int i = wave * SEG_C; i < J; i += (BS / 64) * SEG_C) {
-            double s[SEG_C] = {};
-            for (int q = b0 + lane; q < b1; q += 64)
+        if ((int64_t)(b1 - b0) * J > SEG_DIRECT) {
+            for (int i = threadIdx.x; i < J; i += BS) hs[i] = a.coef[(size_t)inst * a.ld_coef + i];
+        } else {
+            for (int i = wave * SEG_C; i < J; i += (BS / 64) * SEG_C) {
+                double s[SEG_C] = {};
+                for (int q = b0 + lane; q < b1; q += 64)
 #pragma unroll
-                for (int c = 0; c < SEG_C; ++c) s[c] += a.part_in[(size_t)(i + c < J ? i + c : i) * nblk + q];
+                    for (int c = 0; c < SEG_C; ++c) s[c] += a.part_in[(size_t)(i + c < J ? i + c : i) * nblk + q];
 #pragma unroll
-            for (int c = 0; c < SEG_C; ++c) {
-                const double h = wave_ops::wave_sum_all(s[c]);
-                if (lane == 0 && i + c < J) hs[i + c] = h;
+                for (int c = 0; c < SEG_C; ++c) {
+                    const double h = wave_ops::wave_sum_all(s[c]);
+                    if (lane == 0 && i + c < J) hs[i + c] = h;
+                }
             }
         }
         __syncthreads();
@@ -454,6 +459,20 @@ __global__ __launch_bounds__(BS) void k_seg_sweep(SegSweep a) {
             }
         }
     }
+}
+
+// coef[inst][i] = sum of part_in[i] over the instance's blocks, for instances above SEG_DIRECT; one wave
+// per sum
+__global__ void k_seg_coef(SegSweep a, int n_inst) {
+    const int64_t w = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    if (w >= (int64_t)n_inst * a.J) return;
+    const int inst = (int)(w / a.J), i = (int)(w - (int64_t)inst * a.J), lane = threadIdx.x & 63;
+    const int b0 = a.ib0[inst], b1 = a.ib1[inst];
+    if ((int64_t)(b1 - b0) * a.J <= SEG_DIRECT || a.ctl[inst].done) return;
+    double s = 0.0;
+    for (int q = b0 + lane; q < b1; q += 64) s += a.part_in[(size_t)i * a.nblk + q];
+    s = wave_ops::wave_sum_all(s);
+    if (lane == 0) a.coef[(size_t)inst * a.ld_coef + i] = s;
 }
 
 // out[inst * ldo] = sum of part[b] over the instance's blocks; one wave per instance
@@ -737,6 +756,10 @@ hdg_status seg_sweep(hdg_ctx ctx, const BatchDev& b, SegSweep a, bool axpy, bool
     a.ib0 = b.ib0;
     a.ib1 = b.ib1;
     a.nblk = b.nblk;
+    if (axpy && (int64_t)b.max_chunks * a.J > SEG_DIRECT) {
+        hipLaunchKernelGGL(k_seg_coef, dim3(div_up((long long)b.n_inst * a.J, 4)), dim3(256), 0, ctx->stream, a, b.n_inst);
+        HDG_LAUNCH_CHECK(ctx);
+    }
     const void* k = !axpy ? (const void*)k_seg_sweep<false, true>
                     : dot ? (const void*)k_seg_sweep<true, true>
                           : (const void*)k_seg_sweep<true, false>;
