@@ -49,11 +49,19 @@ struct ElemArgs {
     int ne, P, PF, L, D, residual_only, keep_mass;
 };
 
-// Threads of an element's block: one wave where every phase has one tile of basis functions (no
-// barrier then waits on another wave, and a CU holds four times the elements; 14400 p = 1 quads:
-// 0.27 ms with four waves, 0.19 with one). P = 25 by one wave: 1.3 ms for 16384 quads, by two 0.87,
-// by four 0.70.
-inline int elem_threads(int P) { return P <= 16 ? 64 : EBS; }
+// Threads of an element's block: as few waves as still keep a CU busy, since a phase of one or two tiles
+// leaves the others at its barrier. A CU of 160 KiB holds 160 KiB / lds elements, and no more than its
+// share of the mesh; 12 of one wave are enough, 6 of two, fewer take four. us with 64, 128 and 256 threads,
+// 16,384 elements, Jacobian with kept mass matrices, then residual only:
+//   quads p = 2 (19 a CU)  183 222 312, 124 151 205     triangles p = 3 (13)  250 256 333, 170 177 225
+//   quads p = 3 (8)        367 300 386, 233 195 245     hexes p = 1 (8)       544 437 546, 290 237 299
+//   quads p = 4 (4)       1035 770 586, 589 434 346     tets p = 2 (4)        966 737 659, 612 460 369
+// quads p = 1 (48) by the size of the mesh: 256 elements 65 61 59, 2048 71 71 81, 4096 83 92 110.
+inline int elem_threads(size_t lds, int64_t ne) {
+    const int64_t held = (int64_t)(160 * 1024 / lds), share = (ne + 255) / 256;
+    const int64_t per_cu = held < share ? held : share;
+    return per_cu >= 12 ? 64 : per_cu >= 6 ? 128 : EBS;
+}
 
 // LDS offsets (in doubles) of the element's staged arrays
 struct ElemLds {
@@ -97,7 +105,7 @@ __host__ __device__ inline ElemLds elem_lds(int P, int PF, int L, int D, int Qv,
 __device__ __forceinline__ double sel3(const double (&v)[3], int d) { return d == 0 ? v[0] : d == 1 ? v[1] : v[2]; }
 
 // Bound by the matrix-core tiles and by the element's arrays (each read and written once); every sum is
-// an mma16 tile with its operands in LDS, the tiles shared out over the four waves, where a thread per
+// an mma16 tile with its operands in LDS, the tiles shared out over the waves, where a thread per
 // entry spent two LDS loads on each multiply-add. Tiles are 16 wide, so P = 25 works at 61% of its
 // products. 16384 Burgers p = 4 quads, Jacobian with kept mass matrices: 0.87 ms by entries, 0.58 so
 // (1.7 TB/s; the copies to LDS alone 0.15 ms, the rest matrix-core and vector instructions in near
@@ -402,7 +410,7 @@ __device__ __forceinline__ void element_body(const ElemView& a, double* sm) {
                     if (jr >= PF || ir >= P) continue;
 #pragma unroll
                     for (int d = 0; d < D; ++d) {
-                            if (put_mass) a.Cd[(d * P + ir) * nt + c] = cd[d][r];
+                        if (put_mass) a.Cd[(d * P + ir) * nt + c] = cd[d][r];
                         a.G[c * DP + d * P + ir] = interior ? -nu * cd[d][r] : 0.0;
                     }
                     a.F[ir * nt + c] = f[r];
@@ -630,7 +638,7 @@ hdg_status element_blocks_run(hdg_ctx ctx, const hdg_dims* d, const hdg_elem_geo
                     : d->dim == 3 ? (const void*)k_element_blocks<3>
                                   : (const void*)k_element_blocks<1>;
     void* args[] = {(void*)&a};
-    HDG_HIP_CHECK(ctx, hipLaunchKernel(k, dim3(d->ne), dim3(elem_threads(d->npe)), args, lds, ctx->stream));
+    HDG_HIP_CHECK(ctx, hipLaunchKernel(k, dim3(d->ne), dim3(elem_threads(lds, d->ne)), args, lds, ctx->stream));
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }
