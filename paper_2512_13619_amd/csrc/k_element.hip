@@ -483,8 +483,10 @@ __global__ void __launch_bounds__(EBS, 4) k_element_blocks(ElemArgs a) {
 
 // Batched instances: element e belongs to instance eid[e]; its arrays sit at the instance's
 // offsets plus its instance-local index times the per-element sizes.
-__global__ void __launch_bounds__(128, 3) k_element_blocks_batch(const ElemInst* __restrict__ inst,
-                                                              const int32_t* __restrict__ eid, ElemBatchArgs a) {
+// 128 registers, two of them spilled: four waves a SIMD (eight p = 4 quad instances, 8000 elements, residual:
+// 266 us with 131 registers and three waves, 236 so).
+__global__ void __launch_bounds__(EBS, 4) k_element_blocks_batch(const ElemInst* __restrict__ inst,
+                                                               const int32_t* __restrict__ eid, ElemBatchArgs a) {
     extern __shared__ double sm[];
     const int64_t e = blockIdx.x;
     const ElemInst& q = inst[eid[e]];
@@ -585,7 +587,9 @@ size_t element_batch_lds_bytes(int P, int PF, int L, int D, int nqv, int nqf) {
 hdg_status element_blocks_batch_run(hdg_ctx ctx, int64_t total_ne, const ElemInst* inst_dev, const int32_t* eid,
                                     const ElemBatchArgs& a, size_t lds) {
     if (total_ne == 0) return HDG_OK;
-    hipLaunchKernelGGL(k_element_blocks_batch, dim3((unsigned)total_ne), dim3(128), lds, ctx->stream, inst_dev, eid, a);
+    // lds is the largest instance's
+    hipLaunchKernelGGL(k_element_blocks_batch, dim3((unsigned)total_ne), dim3(elem_threads(lds, total_ne)), lds, ctx->stream,
+                       inst_dev, eid, a);
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }
