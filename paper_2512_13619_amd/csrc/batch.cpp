@@ -65,6 +65,7 @@ hdg_status hdg_batch_create(hdg_ctx ctx, int32_t n_inst, const hdg_dims* dims_h,
     std::vector<FaceBlk> fblk;
     int64_t e0 = 0, f0 = 0;
     size_t max_cond = 0, max_rec = 0;
+    double tile_work = 0.0;
     for (int i = 0; i < n_inst; ++i) {
         const hdg_dims& d = dims_h[i];
         if (d.ne < 1 || d.nf < 1 || d.ncomp < 1 || d.dim < 1 || d.dim > 3 || d.npe < 1 || d.npf < 1 || d.nlfe < 2 ||
@@ -92,6 +93,8 @@ hdg_status hdg_batch_create(hdg_ctx ctx, int32_t n_inst, const hdg_dims* dims_h,
             return HDG_ERR_SHAPE;
         }
         max_cond = std::max(max_cond, cond);
+        const double madds = (double)q.ne * q.R * q.R * q.KD;
+        tile_work += cond_tiles(q.R, q.KD) ? madds : -madds;
         max_rec = std::max(max_rec, (size_t)q.nt + q.nu + q.P);
         const int64_t per[A_NARR] = {
             (int64_t)q.ne * q.P * q.P, (int64_t)q.ne * q.D * q.P * q.P, (int64_t)q.ne * q.D * q.P * q.L * q.PF,
@@ -137,6 +140,7 @@ hdg_status hdg_batch_create(hdg_ctx ctx, int32_t n_inst, const hdg_dims* dims_h,
     dv.total_dof = b->offs[A_VEC][n_inst];
     dv.nblk = (int)blk_inst.size();
     dv.max_cond_lds = max_cond;
+    dv.tiles = tile_work > 0.0;
     dv.max_rec_lds = max_rec;
     if (err == hipSuccess) dv.desc = dev_upload(b, b->host, &err);
     if (err == hipSuccess) dv.eid = dev_upload(b, eid, &err);

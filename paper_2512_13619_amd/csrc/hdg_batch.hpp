@@ -39,6 +39,10 @@ inline int batch_team(int nb, int S) {
     return l;
 }
 
+// Whether an element's condensation is better off with its product in tiles: more than 64 multiply-adds a
+// thread of 256 by entries (R rows and columns, depth KD; both sides in k_batch.hip).
+inline bool cond_tiles(int R, int KD) { return (R * R + 255) / 256 * KD > 64; }
+
 // Entries of a reduction chunk. 96 instances of 270,000 unknowns in all give 580 blocks.
 constexpr int SEG_CHUNK = 512;
 
@@ -84,6 +88,7 @@ struct BatchDev {
     int n_inst = 0, nblk = 0, nfblk = 0, max_chunks = 0;
     int64_t total_ne = 0, total_nf = 0, total_dof = 0;
     size_t max_cond_lds = 0, max_rec_lds = 0;
+    bool tiles = false;             // condensation by tiles: one kernel for all elements: the one for most of the multiply-adds
     int max_nb = 0, max_snb = 0, max_R = 0;
 };
 

@@ -25,8 +25,14 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // ---- condensation: one element per workgroup iteration, all in LDS ------------------------
 // Bound by the elimination's chain of pivots: three barriers a pivot, the update in a 16 x 16 grid of
-// threads (entries numbered through cost a division each, and the multipliers a barrier of their own);
-// the product with W on the matrix cores. 96 mixed instances: 4.05 ms before, 3.17 ms so.
+// threads (entries numbered through cost a division each, and the multipliers a barrier of their own), and
+// by the latency of the element's arrays, which are read once. The product with W: 16x16 tiles on the
+// matrix cores, or an entry per thread for small elements (cond_tiles), where few waves have a tile and the
+// tiles' 112 registers let only four waves share a SIMD (seven by entries). 8000 elements, us by tiles and by
+// entries (multiply-adds a thread): p = 1 quads 119, 100 (8); p = 2 quads 217, 212 (36); p = 1 quads with three
+// components 285, 253 (48); p = 1 hexes 243, 301 (96); p = 4 triangles 391, 467 (120); p = 4 quads 1073, 1820
+// (400). 96 mixed instances, most of them in tiles: 4.05 ms by entries, 3.1 by tiles.
+template <bool TILES>
 __global__ __launch_bounds__(BS) void k_batch_condense(const InstDesc* __restrict__ desc,
                                                        const int32_t* __restrict__ eid, int64_t total_ne,
                                                        BatchElemPtrs in, double* __restrict__ Kbar,
@@ -55,19 +61,45 @@ __global__ __launch_bounds__(BS) void k_batch_condense(const InstDesc* __restric
         const double* rt = in.rt + q.off[10] + le * nt;
         const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
         // W = Minv [B_d | C_d]
-        for (int r = ty; r < KD; r += BS / 16) {
-            const int d = r / P, i = r - d * P;
-            for (int c = tx; c < NW; c += 16) {
+        {
+            const int dr = BS / NW, dc = BS - dr * NW;
+            for (int idx = threadIdx.x, r = idx / NW, c = idx - r * NW; idx < KD * NW; idx += BS, r += dr, c += dc) {
+                if (c >= NW) {
+                    c -= NW;
+                    ++r;
+                }
+                const int d = (r >= P) + (r >= 2 * P), i = r - d * P;
                 const double* b = c < P ? Bd + (size_t)d * P * P + c : Cd + (size_t)d * P * LPF + (c - P);
                 const int ldb = c < P ? P : LPF;
                 double acc = 0.0;
                 for (int k = 0; k < P; ++k) acc += Mi[(size_t)i * P + k] * b[(size_t)k * ldb];
-                W[r * NW + c] = acc;
+                W[idx] = acc;
             }
         }
         __syncthreads();
-        // T = T0 - X W, column-mapped per component: 16x16 tiles on the matrix cores
-        {
+        // T = T0 - X W, column-mapped per component
+        const int NC = nu + nt;
+        auto x_row = [&](int r) { return r < nu ? Dm + (size_t)r * nq : Gm + (size_t)(r - nu) * nq; };
+        auto t0_at = [&](int r, int t) {          // t < nu: columns of u, then of the trace
+            if (t < nu) return r < nu ? Em[(size_t)r * nu + t] : Hm[(size_t)(r - nu) * nu + t];
+            return r < nu ? Fm[(size_t)r * nt + t - nu] : Jm[(size_t)(r - nu) * nt + t - nu];
+        };
+        if constexpr (!TILES) {
+            const int dr = BS / NC, dc = BS - dr * NC;
+            for (int idx = threadIdx.x, r = idx / NC, t = idx - r * NC; idx < R * NC; idx += BS, r += dr, t += dc) {
+                if (t >= NC) {
+                    t -= NC;
+                    ++r;
+                }
+                const int l = (t - nu) / (M * PF), tr = t - nu - l * M * PF;
+                const int m = t < nu ? t / P : tr / PF, c = t < nu ? t - m * P : P + l * PF + tr - m * PF;
+                const double* X = x_row(r) + m * KD;
+                const double t0 = t0_at(r, t);
+                double acc = 0.0;
+                for (int k = 0; k < KD; ++k) acc += X[k] * W[k * NW + c];
+                T[r * C + t] = t0 - acc;
+            }
+        } else {
             const int wave = threadIdx.x >> 6, l16 = threadIdx.x & 15, lq = (threadIdx.x & 63) >> 4;
             int job = 0;
             for (int m = 0; m < M; ++m)
@@ -75,20 +107,16 @@ __global__ __launch_bounds__(BS) void k_batch_condense(const InstDesc* __restric
                     for (int c0 = 0; c0 < NW; c0 += 16) {
                         if ((job++ & (BS / 64 - 1)) != wave) continue;
                         const int r = r0 + l16 < R ? r0 + l16 : R - 1, c = c0 + l16 < NW ? c0 + l16 : NW - 1;
-                        const double* X = (r < nu ? Dm + (size_t)r * nq : Gm + (size_t)(r - nu) * nq) + m * KD;
-                        wave_ops::d4 acc = {};
-                        wave_ops::mma16s<false, false>(KD, wave_ops::seq(X, 1), wave_ops::seq(W + c, NW), acc);
-                        if (c0 + l16 >= NW) continue;
-                        const int l = (c - P) / PF, tt = c < P ? m * P + c : (l * M + m) * PF + (c - P - l * PF);
+                        const int l = (c - P) / PF, t = c < P ? m * P + c : nu + (l * M + m) * PF + (c - P - l * PF);
+                        double t0[4];                 // on its way with the product's operands
 #pragma unroll
-                        for (int q4 = 0; q4 < 4; ++q4) {
-                            const int ro = r0 + 4 * q4 + lq;
-                            if (ro >= R) continue;
-                            double t0;
-                            if (ro < nu) t0 = c < P ? Em[(size_t)ro * nu + tt] : Fm[(size_t)ro * nt + tt];
-                            else t0 = c < P ? Hm[(size_t)(ro - nu) * nu + tt] : Jm[(size_t)(ro - nu) * nt + tt];
-                            T[ro * C + (c < P ? tt : nu + tt)] = t0 - acc[q4];
-                        }
+                        for (int q4 = 0; q4 < 4; ++q4) t0[q4] = t0_at(r0 + 4 * q4 + lq < R ? r0 + 4 * q4 + lq : R - 1, t);
+                        wave_ops::d4 acc = {};
+                        wave_ops::mma16s<false, false>(KD, wave_ops::seq(x_row(r) + m * KD, 1), wave_ops::seq(W + c, NW), acc);
+                        if (c0 + l16 >= NW) continue;
+#pragma unroll
+                        for (int q4 = 0; q4 < 4; ++q4)
+                            if (r0 + 4 * q4 + lq < R) T[(r0 + 4 * q4 + lq) * C + t] = t0[q4] - acc[q4];
                     }
         }
         for (int r = threadIdx.x; r < R; r += BS) T[(size_t)r * C + C - 1] = r < nu ? ru[r] : rt[r - nu];
@@ -709,11 +737,12 @@ __global__ __launch_bounds__(BS) void k_batch_recover(const InstDesc* __restrict
 hdg_status batch_launch_condense(hdg_ctx ctx, const BatchDev& b, const BatchElemPtrs& in, double* Kbar, double* rbar,
                                  double* local, int* bad, int grid) {
     const size_t lds = sizeof(double) * b.max_cond_lds;
+    const void* k = b.tiles ? (const void*)k_batch_condense<true> : (const void*)k_batch_condense<false>;
     if (lds > 64 * 1024)
-        HDG_HIP_CHECK(ctx, hipFuncSetAttribute((const void*)k_batch_condense,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(k_batch_condense, dim3(grid), dim3(BS), lds, ctx->stream, b.desc, b.eid, b.total_ne, in, Kbar,
-                       rbar, local, bad);
+        HDG_HIP_CHECK(ctx, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    void* args[] = {(void*)&b.desc, (void*)&b.eid, (void*)&b.total_ne, (void*)&in, (void*)&Kbar, (void*)&rbar,
+                    (void*)&local, (void*)&bad};
+    HDG_HIP_CHECK(ctx, hipLaunchKernel(k, dim3(grid), dim3(BS), args, lds, ctx->stream));
     HDG_LAUNCH_CHECK(ctx);
     return HDG_OK;
 }
