@@ -29,8 +29,8 @@ __device__ __forceinline__ double wave_sum(double v) {
 // by the latency of the element's arrays, which are read once. The product with W: 16x16 tiles on the
 // matrix cores, or an entry per thread for small elements (cond_tiles), where few waves have a tile and the
 // tiles' 112 registers let only four waves share a SIMD (seven by entries). 8000 elements, us by tiles and by
-// entries (multiply-adds a thread): p = 1 quads 119, 100 (8); p = 2 quads 217, 212 (36); p = 1 quads with three
-// components 285, 253 (48); p = 1 hexes 243, 301 (96); p = 4 triangles 391, 467 (120); p = 4 quads 1073, 1820
+// entries (multiply-adds a thread): p = 1 quads 119, 97 (8); p = 2 quads 217, 207 (36); p = 1 quads with three
+// components 285, 246 (48); p = 1 hexes 240, 301 (96); p = 4 triangles 382, 467 (120); p = 4 quads 1066, 1820
 // (400). 96 mixed instances, most of them in tiles: 4.05 ms by entries, 3.1 by tiles.
 template <bool TILES>
 __global__ __launch_bounds__(BS) void k_batch_condense(const InstDesc* __restrict__ desc,
@@ -121,16 +121,14 @@ __global__ __launch_bounds__(BS) void k_batch_condense(const InstDesc* __restric
         }
         for (int r = threadIdx.x; r < R; r += BS) T[(size_t)r * C + C - 1] = r < nu ? ru[r] : rt[r - nu];
         __syncthreads();
-        // eliminate the first nu columns, pivots among the Ebar rows; the multipliers of column k are
-        // written back while wave 0 looks for the next pivot
+        // eliminate the first nu columns, pivots among the Ebar rows; the multipliers of column k that are
+        // stored (the Ebar rows') are written back while wave 0 looks for the next pivot
         bool singular = false;
         double inv = 0.0;
-        for (int k = 0; k <= nu; ++k) {
-            if (k > 0 && (threadIdx.x >= 64 || k == nu))
-                for (int i = k + (k == nu ? threadIdx.x : threadIdx.x - 64); i < R; i += k == nu ? BS : BS - 64)
-                    T[i * C + k - 1] *= inv;
-            if (k == nu) break;
-            if (threadIdx.x < 64) {
+        for (int k = 0; k < nu; ++k) {
+            if (threadIdx.x >= 64 && k > 0) {
+                for (int i = k + threadIdx.x - 64; i < nu; i += BS - 64) T[i * C + k - 1] *= inv;
+            } else if (threadIdx.x < 64) {
                 double best = -1.0;
                 int bi = k;
                 for (int i = k + threadIdx.x; i < nu; i += 64) {
@@ -163,7 +161,6 @@ __global__ __launch_bounds__(BS) void k_batch_condense(const InstDesc* __restric
             }
             __syncthreads();
         }
-        __syncthreads();
         if (singular && threadIdx.x == 0) atomicMin(bad_elem, (int)g);
         double* lo = local + q.local_off + le * nu * C;
         for (int idx = threadIdx.x; idx < nu * C; idx += BS) lo[idx] = T[idx];
