@@ -966,6 +966,9 @@ __global__ __launch_bounds__(64) void k_cond_trinv(CondDims cd, const double* __
 // slab of sw <= 32 columns). LDS: the slab, nu rows x SLAB_LD.
 constexpr int SLAB_LD = 33;
 
+// IDENT: the columns are the identity's. L leaves the 32-row blocks of a slab above its first entry zero, and
+// the forward sweep starts there (half of it; the search costs a condensation, whose columns are full, 1%).
+template <bool IDENT>
 __global__ __launch_bounds__(256, 2) void k_cond_getrs(CondDims cd, long long nblk, int nsl, int sw,
                                                        double* __restrict__ top, const int32_t* __restrict__ perm,
                                                        const double* __restrict__ dinv) {
@@ -982,22 +985,21 @@ __global__ __launch_bounds__(256, 2) void k_cond_getrs(CondDims cd, long long nb
     const int nkb = (nu + 31) / 32;
     const double* De = dinv + (size_t)e * nkb * 2048;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // the slab's rows in the interchanged order, and the first of its 32-row blocks with an entry:
-    // L leaves the blocks above it zero (half the forward sweep for the columns of the identity)
+    // the slab's rows in the interchanged order
     __shared__ int first;
-    if (threadIdx.x == 0) first = nkb;
-    __syncthreads();
+    if (IDENT && threadIdx.x == 0) first = nkb;
+    if (IDENT) __syncthreads();
     int mine = nkb;
     for (int idx = threadIdx.x; idx < nu * 32; idx += 256) {
         const int i = idx >> 5, j = idx & 31;
         const bool ok = j < ncs;
         const double v = Te[(size_t)pe[i] * C + c0 + (ok ? j : 0)];
         Y[i * SLAB_LD + j] = ok ? v : 0.0;
-        if (ok && v != 0.0 && i >> 5 < mine) mine = i >> 5;
+        if (IDENT && ok && v != 0.0 && i >> 5 < mine) mine = i >> 5;
     }
-    if (mine < nkb) atomicMin(&first, mine);
+    if (IDENT && mine < nkb) atomicMin(&first, mine);
     __syncthreads();
-    const int kb0 = first;
+    const int kb0 = IDENT ? first : 0;
     // Y_kb <- inv(diagonal block) Y_kb, by one wave (a 32 x 32 x 32 product)
     auto diag = [&](int kb, int which) {
         const int r0 = kb * 32;
@@ -1506,8 +1508,9 @@ hdg_status set_kernel_lds(hdg_ctx ctx, const CondDims& cd, int NB) {
     if (cd.nu > 64 && lds > 64 * 1024)
         HDG_HIP_CHECK(ctx, hipFuncSetAttribute(lu_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     if (getrs_lds_bytes(cd) > 64 * 1024)
-        HDG_HIP_CHECK(ctx, hipFuncSetAttribute((const void*)k_cond_getrs, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)getrs_lds_bytes(cd)));
+        for (const void* fn : {(const void*)k_cond_getrs<false>, (const void*)k_cond_getrs<true>})
+            HDG_HIP_CHECK(ctx, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                   (int)getrs_lds_bytes(cd)));
     HDG_HIP_CHECK(ctx, hipFuncSetAttribute((const void*)k_cond_schur, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)GEMM_LDS));
     return HDG_OK;
@@ -1572,8 +1575,13 @@ hdg_status eliminate_and_schur(hdg_ctx ctx, const CondDims& cd, int NB, int64_t 
     const int sw = div_up(ncx, div_up(ncx, 32));
     const int nsl = div_up(ncx, sw);
     const long long nslab = (long long)n * nsl;
-    hipLaunchKernelGGL(k_cond_getrs, dim3((unsigned)((nslab + 7) / 8 * 8)), dim3(BS), getrs_lds_bytes(cd), ctx->stream,
-                       cd, nslab, nsl, sw, top, (const int32_t*)perm, (const double*)dinv);
+    const dim3 sgrid((unsigned)((nslab + 7) / 8 * 8));
+    if (bot)
+        hipLaunchKernelGGL(k_cond_getrs<false>, sgrid, dim3(BS), getrs_lds_bytes(cd), ctx->stream, cd, nslab, nsl, sw, top,
+                           (const int32_t*)perm, (const double*)dinv);
+    else
+        hipLaunchKernelGGL(k_cond_getrs<true>, sgrid, dim3(BS), getrs_lds_bytes(cd), ctx->stream, cd, nslab, nsl, sw, top,
+                           (const int32_t*)perm, (const double*)dinv);
     HDG_LAUNCH_CHECK(ctx);
     if (!bot) return HDG_OK;        // X alone
     const int tm_n = div_up(cd.nt, GT);
