@@ -1600,23 +1600,24 @@ hdg_status eliminate_and_schur(hdg_ctx ctx, const CondDims& cd, int NB, int64_t 
 // never form the trace rows (288: their fill and product were 1.7 of 6.9 ms for 729 elements).
 //   P = Kbar^e, except that the diagonal block of each local face l is the assembled K_ff of
 //   its face f = e2f[e][l] (= Kbar^{e1}_{l1 l1} + Kbar^{e2}_{l2 l2}; one term on a boundary).
-// A wave fills a row.
+// A row is filled by 64 lanes, or 16 or 32 where that many cover its first half (4000 elements of 12 rows, whole
+// setup: 142 us by whole waves, 139 so).
 __global__ __launch_bounds__(BS) void k_asm_fill(int nb, int L, const double* __restrict__ Kbar,
                                                  const double* __restrict__ K64, int S, const int32_t* __restrict__ e2f,
                                                  double* __restrict__ top, double* __restrict__ bot) {
     const long long e = blockIdx.x;
-    const int nt = L * nb, C = 2 * nt + 1, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int nt = L * nb, C = 2 * nt + 1, G = nt < 16 ? 16 : nt < 32 ? 32 : 64, lane = threadIdx.x & (G - 1);
     const double* Ke = Kbar + (size_t)e * nt * nt;
-    for (int r = wave; r < nt; r += BS / 64) {
+    for (int r = threadIdx.x / G; r < nt; r += BS / G) {
         const int lr = r / nb, rr = r - lr * nb, lo = lr * nb;
         const double* Kf = K64 + (size_t)e2f[e * L + lr] * S * nb * nb + rr;
         double* Te = top + ((size_t)e * nt + r) * C;
-        for (int c = lane; c < nt; c += 64)
+        for (int c = lane; c < nt; c += G)
             Te[c] = (c >= lo && c < lo + nb) ? Kf[(size_t)(c - lo) * nb] : Ke[(size_t)r * nt + c];
-        for (int c = lane; c < nt + 1; c += 64) Te[nt + c] = c == r ? 1.0 : 0.0;
+        for (int c = lane; c < nt + 1; c += G) Te[nt + c] = c == r ? 1.0 : 0.0;
         if (bot) {
             double* Be = bot + ((size_t)e * nt + r) * C;
-            for (int c = lane; c < C; c += 64) Be[c] = c == r ? 1.0 : 0.0;
+            for (int c = lane; c < C; c += G) Be[c] = c == r ? 1.0 : 0.0;
         }
     }
 }
