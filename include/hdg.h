@@ -414,7 +414,7 @@ hdg_status hdg_residual_norm_noalloc(hdg_ctx ctx, const hdg_dims* dims, const in
  *   time_term->u_prev [ne][ncomp][npe], r_extra [ne][ncomp*npe]; out->q [ne][ncomp][dim][npe].
  *   The flux derivatives come from forward-mode dual numbers per quadrature point. Uses a
  *   context workspace for the per-point flux derivatives (elements in equal chunks of at most 2 GiB
- *   of it; none when residual-only).
+ *   of it, 1 GiB if that cannot be had; none when residual-only).
  *   HDG_ERR_ARG for an unknown model, a model whose ncomp does not match, or dim != 3;
  *   HDG_ERR_SHAPE if an element's staged data exceed 150 KiB of LDS; HDG_ERR_SINGULAR as for
  *   hdg_element_blocks (synchronises). hdg_residual_norm applies to its ru, rt unchanged. */
