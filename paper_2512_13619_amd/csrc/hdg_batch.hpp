@@ -31,8 +31,9 @@ struct FaceBlk {
     int32_t inst, f0, lteam, pad;
 };
 
-// Threads of a face with blocks of edge nb (log2): 8, 16 or 32, at least nb and half its S*nb columns
-// (the block's gathered x then fits 512 doubles), so that a thread has at most 14 entries.
+// Threads of a face with blocks of edge nb (log2): 8, 16 or 32, the fewest that are at least 4 nb and half
+// its S*nb columns, or 32: the block's gathered x fits 512 doubles (S*nb <= 64), and a thread has at most 16
+// entries (nb = 7, nlfe = 5).
 inline int batch_team(int nb, int S) {
     int l = 3;
     while (l < 5 && ((1 << l) < 4 * nb || 2 << l < S * nb)) ++l;

@@ -199,8 +199,8 @@ struct SysArgs {
 // sum the fields as rows and the basis functions as columns), where a thread-per-entry loop spent
 // two loads on every multiply-add (24,480 Navier-Stokes p = 2 tets, residual only: 2.04 ms so, with
 // k_sys_blocks' sums; 0.61 ms now, 1.3 TB/s).
-// JAC: the flux derivatives too; without them the kernel needs half the registers and twice the
-// blocks share a CU.
+// JAC: the flux derivatives too. Without them the Navier-Stokes kernel holds 107 registers, four blocks a CU,
+// instead of 165 and three; elasticity's derivatives cost nothing (65 and 69, seven).
 template <int M, bool JAC>
 __global__ void __launch_bounds__(SBS, JAC ? 2 : 4) k_sys_points(SysArgs a) {
     extern __shared__ double sm[];
@@ -546,9 +546,9 @@ inline BlkStage blk_stage(int M, int P, int PF, int Qv, int L, int Qf) {
 // pair's 12 (or 4) point values, which one load per four points brings to each row of 16 lanes and
 // row broadcasts hand to every lane. A wave owns TI row tiles of all four slots, so a point's basis
 // gradients serve 4 TI products; TI = 1 where P <= 16 (a second tile would be padding). Two row tiles
-// and one column tile keep the kernel at 128 VGPRs, four waves a SIMD, which hide the operand
-// chain and the stores (2 x 2 tiles at two waves a SIMD: 6.5 ms below, this 5.5). G, F and J share
-// per (face, b) the operand rows (a, j).
+// and one column tile, held to 128 VGPRs with 13 to 17 spilled (none with TI = 1), let four waves share a
+// SIMD, which hide the operand chain and the stores (2 x 2 tiles at two waves a SIMD: 6.5 ms below, this
+// 5.5). G, F and J share per (face, b) the operand rows (a, j).
 // Bound by its stores: 16^3 Navier-Stokes p = 2 hexes write 10.7 GB, 4.2 ms with every product left
 // out (rows of 27 or 9 doubles at 8-byte alignment reach 3.1 TB/s in a store-only loop, whole lines
 // 4.5 to 5.8) and 2.9 ms of products with the stores left out; 5.5 ms together (1.9 TB/s), where the
@@ -875,7 +875,11 @@ hdg_status element_sys_run(hdg_ctx ctx, const hdg_dims* d, const hdg_elem_geom* 
     const size_t bl = sizeof(double) * (size_t)st.doubles;
     if (bl > 64 * 1024) HDG_HIP_CHECK(ctx, hipFuncSetAttribute(kb, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bl));
     // 256 CUs hold 512 blocks, two each: a mesh of fewer elements shares an element's items out over
-    // up to seven blocks (27 Navier-Stokes p = 2 hexes: 0.17 ms; the thread-per-entry loop 8.2 ms)
+    // up to seven blocks: the 50 products of D and E of a Navier-Stokes p = 2 hex are seven rounds of eight
+    // waves (27 of them: one block 363 us, four 197, seven 168, twelve 167; thread-per-entry loop 8260). Over
+    // one to twelve blocks of twelve shapes with 8 to 64 elements seven is within 5% of the best, but for
+    // p = 3 hexes (192 and 400 products, nine blocks: 27 elements 434 us, seven 502). 125 to 300 elements,
+    // where the bound of 512 gives five to two blocks, would be up to 20% faster with four to eight.
     const int64_t parts = n >= 512 ? 1 : (512 + n - 1) / n < 7 ? (512 + n - 1) / n : 7;
     void* bargs[] = {(void*)&a, (void*)&st};
     HDG_HIP_CHECK(ctx, hipLaunchKernel(kb, dim3((unsigned)n, (unsigned)parts), dim3(BBS), bargs, bl, ctx->stream));
