@@ -500,8 +500,8 @@ __global__ __launch_bounds__(COEF_BS) void k_dcgs2_coef(GmresCtl* ctl, const dou
     __syncthreads();
     rho = sh_rho;
     // wave 0 closes column j-1 while wave 1 forms the new column: neither needs the other's result (after
-    // the last step of a cycle the new column is not read). One wave doing both in turn cost 0.6 us more
-    // of the launch's 11 at 34,000 unknowns (a Burgers DIRK step: 18.7 and 18.3 ms).
+    // the last step of a cycle the new column is not read). One wave doing both in turn cost 1.3 us a step
+    // more (replayed cycles of 50 columns, 34,000 unknowns: 38.5 and 37.2 us a step).
     if (tid == 0) {
         int stop = 0;
         if (j > 0) {
