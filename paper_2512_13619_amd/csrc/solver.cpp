@@ -104,10 +104,10 @@ hdg_status op_B(hdg_ctx ctx, const Op& op, const double* x, const FaceEpilogue& 
 // Whether a cycle in one workgroup is no slower than the general path's ten launches a step (table in
 // k_small.hip): the vectors fit its LDS, a sweep over the operator's rows is at most 60,000 entries, what one
 // CU reads from L2 in about the time of the launches, and the basis, which a CGS2 step reads four times and a
-// CGS step twice, costs that CU no more than the launches either: a cycle that runs its whole length breaks
-// even near 1500 unknowns with CGS2 and 1900 with CGS, whatever the length from 50 columns on, since the
-// general path's sweeps grow with the columns too; a short cycle is ahead up to the LDS limit. Delayed CGS2
-// (four launches a step), modified Gram-Schmidt and other preconditioners stay with the general path.
+// CGS step twice, costs that CU no more than the launches either: a cycle of 50 to 200 columns that runs its
+// whole length breaks even at 1500 to 1600 unknowns with CGS2 and 1800 to 2000 with CGS (the general path's
+// sweeps grow with the columns too), a shorter one further up. Delayed CGS2 (four launches a step), modified
+// Gram-Schmidt and other preconditioners stay with the general path.
 bool small_cycle_fits(size_t N, int S, int nb, int orth, int prec, int restart) {
     if ((prec != HDG_PREC_NONE && prec != HDG_PREC_BJ) || N > SMALL_CYCLE_MAX || N * (size_t)(nb * S) > 60000)
         return false;
