@@ -31,7 +31,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 // tiles' 112 registers let only four waves share a SIMD (seven by entries). 8000 elements, us by tiles and by
 // entries (multiply-adds a thread): p = 1 quads 119, 97 (8); p = 2 quads 217, 207 (36); p = 1 quads with three
 // components 285, 246 (48); p = 1 hexes 240, 301 (96); p = 4 triangles 382, 467 (120); p = 4 quads 1066, 1820
-// (400). 96 mixed instances, most of them in tiles: 4.05 ms by entries, 3.1 by tiles.
+// (400). 96 mixed instances: 4.05 ms by entries, 2.6 by tiles.
 template <bool TILES>
 __global__ __launch_bounds__(BS) void k_batch_condense(const InstDesc* __restrict__ desc,
                                                        const int32_t* __restrict__ eid, int64_t total_ne,
